@@ -374,8 +374,10 @@ def kernel_key(sym):
     if base == "fft_cols":
         parts = [x.strip() for x in targs.split(",")]
         return "fft_z" if len(parts) > 1 and parts[1] == "2" else "fft_y"
-    if base == "fft_yz":
+    if base in ("fft_yz", "split_z"):
         return "fft_yz"
+    if base in ("split_x_fwd", "split_x_inv"):
+        return "fft_x_" + base[8:]
     if base in ("correct", "refine_correct", "correct_ring", "refine_correct_ring"):
         return "correct"
     if base in ("div", "fft_x_fwd", "fft_x_inv", "ib_rhs", "refine_res", "refine_res_ib"):

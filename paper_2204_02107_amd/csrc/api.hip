@@ -16,6 +16,7 @@
 
 #include "common.h"
 #include "fft.h"
+#include "fft_split.h"
 #include "particles.h"
 #include "postproc.h"
 #include "stencil.h"
@@ -101,6 +102,7 @@ struct Layout {
     int xtw_lds;          // x passes stage their twiddle tables in LDS
     int yz, lg_ca, lg_cb;  // fused plane pass (plane-major spectrum) and its LDS chunks
     AxisPlan px, py, pz;
+    SplitPlan sp;          // three-pass solve (sp.r > 0): the x passes carry a factor of the y transform
     StencilLaunch L;       // momentum and scalar stage kernels
     StencilLaunch L1;      // one-cell-per-thread kernels (div, refinement residual, rate)
     StencilLaunch LC;      // the velocity correction (64 x DNSLAB_FROWS tiles: its register-ring form)
@@ -356,6 +358,10 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
         Lo.lg_tx_y = widen(Lo.lg_tx_y, P->ny, Lo.py);
         Lo.lg_tx_z = widen(Lo.lg_tx_z, P->nz, Lo.pz);
     }
+#ifndef DNSLAB_SPLIT
+#define DNSLAB_SPLIT 1
+#endif
+    if (DNSLAB_SPLIT) Lo.sp = make_split_plan(P->nx, P->ny, P->nz, (int)Lo.esz);
     // Fused plane pass: each of the nx/2 + 1 kx planes (ny * nz values) held
     // by one block in registers, its y and z lines transformed in LDS chunks.
     // It cuts two of the three column passes and their launches, but one
@@ -366,7 +372,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     {
         const int nthr = yz_threads(P->ny, Lo.esz == 4);
         const long long max_plane = Lo.esz == 8 ? DNSLAB_YZ_MAX_PLANE : DNSLAB_YZ_MAX_PLANE32;
-        if (DNSLAB_YZ && P->ny > 1 && P->nz > 1 && nthr > 0 && (long long)P->ny * P->nz <= max_plane &&
+        if (DNSLAB_YZ && Lo.sp.r == 0 && P->ny > 1 && P->nz > 1 && nthr > 0 && (long long)P->ny * P->nz <= max_plane &&
             yz_instance(Lo.esz == 4, nthr, (long long)P->ny * P->nz) >= 0 &&
             Lo.py.tpl <= nthr && Lo.pz.tpl <= nthr) {
             const size_t cap = (size_t)DNSLAB_YZ_LDS_KB * 1024;
@@ -623,6 +629,28 @@ FFTArgs<T> fft_args_of(const Layout& Lo, const Grid& g, void* spec, const void* 
     return a;
 }
 
+// The same for the three-pass solve (Lo.sp.r > 0).
+template <typename T>
+SplitArgs<T> split_args_of(const Layout& Lo, const Grid& g, void* spec, const void* w, const double* s2) {
+    const FFTArgs<T> f = fft_args_of<T>(Lo, g, spec, w, s2);
+    SplitArgs<T> a = {};
+    a.spec = f.spec;
+    a.wx = f.wx;
+    a.wy = f.wy;
+    a.wz = f.wz;
+    a.tw = f.tw;
+    a.sx2 = f.sx2;
+    a.sy2 = f.sy2;
+    a.sz2 = f.sz2;
+    a.inv_ntot = f.inv_ntot;
+    a.nx = g.nx;
+    a.ny = g.ny;
+    a.nz = g.nz;
+    a.q = Lo.sp.q;
+    a.gs = Lo.sp.gs;
+    return a;
+}
+
 template <typename T>
 FFTArgs<T> fft_args(dnslab_ctx* x) {
     FFTArgs<T> a = fft_args_of<T>(x->Lo, x->g, x->spec, x->wx, x->sx2);
@@ -633,6 +661,15 @@ FFTArgs<T> fft_args(dnslab_ctx* x) {
 // One FFT solve of Lap p = r (central-difference symbol, null modes zero).
 template <typename T>
 int poisson_solve(dnslab_ctx* x, const T* r, T* pout) {
+    if (x->Lo.sp.r > 0) {
+        SplitArgs<T> b = split_args_of<T>(x->Lo, x->g, x->spec, x->wx, x->sx2);
+        b.r = r;
+        b.p = pout;
+        LAUNCH(x, K_FXF, launch_split_x<T>(b, x->Lo.sp, false, x->cur, x->rec));
+        LAUNCH(x, K_FYZ, launch_split_z<T>(b, x->Lo.sp, x->cur, x->rec));
+        LAUNCH(x, K_FXI, launch_split_x<T>(b, x->Lo.sp, true, x->cur, x->rec));
+        return DNSLAB_OK;
+    }
     const FFTArgs<T> a = fft_args<T>(x);
     LAUNCH(x, K_FXF, launch_fft_x_fwd<T>(a, r, x->cur, x->rec));
     if (x->Lo.yz) {
@@ -1309,6 +1346,16 @@ int poisson_noalloc(const dnslab_params* P, const T* r, T* pout) {
     const FFTArgs<T> a = fft_args_of<T>(Lo, g, b, b + N.off_w, (const double*)(b + N.off_s2));
     const hipStream_t s = (hipStream_t)P->stream;
     hipError_t e = launch_fft_tables<T>((C2<T>*)(b + N.off_w), (double*)(b + N.off_s2), g, s);
+    if (e == hipSuccess && Lo.sp.r > 0) {
+        SplitArgs<T> c = split_args_of<T>(Lo, g, b, b + N.off_w, (const double*)(b + N.off_s2));
+        c.r = r;
+        c.p = pout;
+        e = launch_split_x<T>(c, Lo.sp, false, s);
+        if (e == hipSuccess) e = launch_split_z<T>(c, Lo.sp, s);
+        if (e == hipSuccess) e = launch_split_x<T>(c, Lo.sp, true, s);
+        if (e != hipSuccess) return fail(nullptr, DNSLAB_EHIP, std::string("launch: ") + hipGetErrorString(e));
+        return DNSLAB_OK;
+    }
     if (e == hipSuccess) e = launch_fft_x_fwd<T>(a, r, s);
     if (e == hipSuccess) {
         if (Lo.yz) {
@@ -1913,7 +1960,10 @@ int pfail(dnslab_pool* p, int code, const std::string& msg) {
             return pfail(pool, DNSLAB_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
     } while (0)
 
-bool is_stencil_kind(int kind) { return (kind >> 8) < KK_IB; }
+bool is_stencil_kind(int kind) { return (kind >> 12) < KK_IB; }
+// Passes of the three-pass solve come in an instance per length; scenarios that
+// differ there only still share the other launches of a step.
+bool is_split_kind(int kind) { return (kind >> 12) >= KK_SPLITXF; }
 
 // Record one step of every active slot and build the batched tables.
 int pool_rebuild(dnslab_pool* P, const std::vector<int>& active) {
@@ -1931,8 +1981,9 @@ int pool_rebuild(dnslab_pool* P, const std::vector<int>& active) {
     // group slots by sequence signature
     auto sig = [&](size_t q) {
         std::vector<long long> v;
+        v.push_back(P->slots[active[q]].ctx->g.n >= POOL_DIRECT_CELLS);   // these run on their own
         for (const LaunchRecord& l : recs[q]) {
-            long long key = (long long)l.kind << 32;
+            long long key = (long long)(is_split_kind(l.kind) ? l.kind & ~(2047 << 1) : l.kind) << 32;
             if (is_stencil_kind(l.kind)) key |= (long long)(l.block.x << 16 | l.block.y);
             v.push_back(key);
             v.push_back((long long)l.rec.size());
@@ -1962,29 +2013,35 @@ int pool_rebuild(dnslab_pool* P, const std::vector<int>& active) {
     };
     for (BatchGroup& G : P->groups) {
         const size_t nseq = recs[G.slots[0]].size();
-        G.seq.resize(nseq);
+        G.seq.clear();
         for (size_t i = 0; i < nseq; ++i) {
-            BatchPos& bp = G.seq[i];
-            const LaunchRecord& l0 = recs[G.slots[0]][i];
-            bp.kind = l0.kind;
-            bp.block = l0.block;
-            bp.lds = 0;
-            bp.ns = (int)G.slots.size();
-            std::vector<unsigned char> tab;
-            std::vector<unsigned> starts;
-            unsigned total = 0;
-            for (int q : G.slots) {
-                const LaunchRecord& l = recs[q][i];
+            // one launch per kernel of this position, in order of first appearance
+            std::vector<int> kinds;
+            for (int q : G.slots)
+                if (std::find(kinds.begin(), kinds.end(), recs[q][i].kind) == kinds.end()) kinds.push_back(recs[q][i].kind);
+            for (const int kind : kinds) {
+                BatchPos bp = {};
+                bp.kind = kind;
+                std::vector<unsigned char> tab;
+                std::vector<unsigned> starts;
+                unsigned total = 0;
+                for (int q : G.slots) {
+                    const LaunchRecord& l = recs[q][i];
+                    if (l.kind != kind) continue;
+                    if (starts.empty()) bp.block = l.block;
+                    starts.push_back(total);
+                    total += l.grid.x * l.grid.y * l.grid.z;
+                    bp.block.x = std::max(bp.block.x, l.block.x);
+                    bp.lds = std::max(bp.lds, l.lds);
+                    tab.insert(tab.end(), l.rec.begin(), l.rec.end());
+                }
+                bp.ns = (int)starts.size();
                 starts.push_back(total);
-                total += l.grid.x * l.grid.y * l.grid.z;
-                bp.block.x = std::max(bp.block.x, l.block.x);
-                bp.lds = std::max(bp.lds, l.lds);
-                tab.insert(tab.end(), l.rec.begin(), l.rec.end());
+                bp.total = total;
+                bp.tab_off = put(tab.data(), tab.size());
+                bp.st_off = put(starts.data(), starts.size() * sizeof(unsigned));
+                G.seq.push_back(bp);
             }
-            starts.push_back(total);
-            bp.total = total;
-            bp.tab_off = put(tab.data(), tab.size());
-            bp.st_off = put(starts.data(), starts.size() * sizeof(unsigned));
         }
         for (int& q : G.slots) q = active[q];   // back to slot ids
         G.direct = G.slots.size() == 1 || P->slots[G.slots[0]].ctx->g.n >= POOL_DIRECT_CELLS;

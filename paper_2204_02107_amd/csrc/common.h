@@ -146,8 +146,9 @@ enum KernelKind : int {
     KK_MOM = 1, KK_SCA, KK_FILT, KK_CORR, KK_DIV, KK_REFRES, KK_REFCORR, KK_ADVANCE, KK_DIAG,   // stencil.hip
     KK_MOMPAIR, KK_SCAPAIR,
     KK_IB = 32, KK_FXF, KK_FXI, KK_COLS,                                              // fft.hip
+    KK_SPLITXF, KK_SPLITXI, KK_SPLITZ,                                                // fft_split.hip
 };
-__host__ __device__ constexpr int kind_code(int base, int mode, int fp32) { return (base << 8) | (mode << 1) | fp32; }
+__host__ __device__ constexpr int kind_code(int base, int mode, int fp32) { return (base << 12) | (mode << 1) | fp32; }
 
 // A launch captured instead of issued: the pool records each scenario's step
 // once and replays every position of the sequence as one batched launch.

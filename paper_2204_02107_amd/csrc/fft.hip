@@ -17,6 +17,8 @@
 // plane by plane and run y-forward, z-solve and y-inverse as one fused pass
 // with one block per kx plane.
 #include "fft.h"
+#include "fft_dev.h"
+#include "fft_split.h"
 
 #include <algorithm>
 
@@ -47,92 +49,6 @@ constexpr int IB_CPT = DNSLAB_IB_CPT;
 namespace dnslab {
 
 namespace {
-
-template <typename T>
-__device__ __forceinline__ C2<T> cadd(C2<T> a, C2<T> b) { return {a.x + b.x, a.y + b.y}; }
-template <typename T>
-__device__ __forceinline__ C2<T> csub(C2<T> a, C2<T> b) { return {a.x - b.x, a.y - b.y}; }
-template <typename T>
-__device__ __forceinline__ C2<T> cscale(C2<T> a, T s) { return {a.x * s, a.y * s}; }
-template <typename T>
-__device__ __forceinline__ C2<T> cmul(C2<T> a, C2<T> b) {
-    return {a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x};
-}
-// a * conj(b)
-template <typename T>
-__device__ __forceinline__ C2<T> cmulc(C2<T> a, C2<T> b) {
-    return {a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y};
-}
-template <typename T>
-__device__ __forceinline__ C2<T> conj_(C2<T> a) { return {a.x, -a.y}; }
-// multiply by -i (forward sign) or +i (inverse sign)
-template <typename T, bool INV>
-__device__ __forceinline__ C2<T> rot(C2<T> a) {
-    return INV ? C2<T>{-a.y, a.x} : C2<T>{a.y, -a.x};
-}
-
-// In-register DFT of length R with kernel e^{-+2 pi i r m / R}.
-template <typename T, int R, bool INV>
-struct DFT;
-
-template <typename T, bool INV>
-struct DFT<T, 2, INV> {
-    static __device__ __forceinline__ void run(C2<T>* v) {
-        const C2<T> a = v[0], b = v[1];
-        v[0] = cadd(a, b);
-        v[1] = csub(a, b);
-    }
-};
-
-template <typename T, bool INV>
-struct DFT<T, 4, INV> {
-    static __device__ __forceinline__ void run(C2<T>* v) {
-        const C2<T> t0 = cadd(v[0], v[2]), t1 = csub(v[0], v[2]);
-        const C2<T> t2 = cadd(v[1], v[3]), t3 = rot<T, INV>(csub(v[1], v[3]));
-        v[0] = cadd(t0, t2);
-        v[2] = csub(t0, t2);
-        v[1] = cadd(t1, t3);
-        v[3] = csub(t1, t3);
-    }
-};
-
-template <typename T, bool INV>
-struct DFT<T, 8, INV> {
-    static __device__ __forceinline__ void run(C2<T>* v) {
-        C2<T> e[4] = {v[0], v[2], v[4], v[6]};
-        C2<T> o[4] = {v[1], v[3], v[5], v[7]};
-        DFT<T, 4, INV>::run(e);
-        DFT<T, 4, INV>::run(o);
-        const T h = T(0.70710678118654752440);
-        // o[m] *= w8^m, w8 = e^{-+ i pi / 4}
-        const C2<T> o1 = INV ? C2<T>{h * (o[1].x - o[1].y), h * (o[1].x + o[1].y)}
-                             : C2<T>{h * (o[1].x + o[1].y), h * (o[1].y - o[1].x)};
-        const C2<T> o2 = rot<T, INV>(o[2]);
-        const C2<T> o3 = INV ? C2<T>{-h * (o[3].x + o[3].y), h * (o[3].x - o[3].y)}
-                             : C2<T>{h * (o[3].y - o[3].x), -h * (o[3].x + o[3].y)};
-        v[0] = cadd(e[0], o[0]);
-        v[4] = csub(e[0], o[0]);
-        v[1] = cadd(e[1], o1);
-        v[5] = csub(e[1], o1);
-        v[2] = cadd(e[2], o2);
-        v[6] = csub(e[2], o2);
-        v[3] = cadd(e[3], o3);
-        v[7] = csub(e[3], o3);
-    }
-};
-
-template <typename T, bool INV>
-struct DFT<T, 3, INV> {
-    static __device__ __forceinline__ void run(C2<T>* v) {
-        const T h = T(0.86602540378443864676);   // sqrt(3)/2
-        const C2<T> t = cadd(v[1], v[2]);
-        const C2<T> sd = rot<T, INV>(csub(v[1], v[2]));
-        const C2<T> m = {v[0].x - T(0.5) * t.x, v[0].y - T(0.5) * t.y};
-        v[0] = cadd(v[0], t);
-        v[1] = {m.x + h * sd.x, m.y + h * sd.y};
-        v[2] = {m.x - h * sd.x, m.y - h * sd.y};
-    }
-};
 
 // One Stockham pass of radix R over all lines held in LDS.  Element e of line
 // l lives at s[l*ls + e*es].  Butterfly b belongs to line b & (nl-1), so
@@ -475,25 +391,6 @@ __device__ __forceinline__ void ib_rhs_body(const IbArgs<T>& A, unsigned blk) {
     }
 }
 
-// X[k] of the real transform from Z = FFT(x_even + i x_odd):
-// E = (Z[k] + conj Z[m-k])/2, O = -i (Z[k] - conj Z[m-k])/2, X[k] = E + w^k O.
-template <typename T>
-__device__ __forceinline__ C2<T> r2c_post(C2<T> za, C2<T> zb, C2<T> w) {
-    const C2<T> zc = conj_(zb);
-    const C2<T> e = cscale(cadd(za, zc), T(0.5));
-    const C2<T> o = cscale(rot<T, false>(csub(za, zc)), T(0.5));
-    return cadd(e, cmul(w, o));
-}
-// Z[k] for the inverse from X[k], X[m-k] (unnormalised: twice the even/odd
-// spectra): E = X[k] + conj X[m-k], O = (X[k] - conj X[m-k]) conj(w^k), Z = E + i O.
-template <typename T>
-__device__ __forceinline__ C2<T> c2r_pre(C2<T> xa, C2<T> xb, C2<T> w) {
-    const C2<T> xc = conj_(xb);
-    const C2<T> e = cadd(xa, xc);
-    const C2<T> o = cmulc(csub(xa, xc), w);
-    return cadd(e, rot<T, true>(o));
-}
-
 // Batched global -> register -> LDS staging: every thread issues all of its
 // loads before the first LDS store, so that a block keeps many independent
 // memory requests in flight (the passes are otherwise latency bound).
@@ -665,14 +562,6 @@ __device__ __forceinline__ void fft_x_inv_body(const FxiArgs<T>& A, unsigned blk
         const int L = line0 + l;
         if (L < nlines) *reinterpret_cast<C2<T>*>(p + (unsigned)L * nx + 2u * (unsigned)n) = s[l * ls + n];
     }
-}
-
-// 1/x to about one ulp: hardware reciprocal refined by two Newton steps.
-__device__ __forceinline__ double recip(double x) {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(r, fma(-x, r, 1.0), r);
-    r = fma(r, fma(-x, r, 1.0), r);
-    return r;
 }
 
 // Column passes along y (MODE 0 forward, 1 inverse) or z (MODE 2: forward,
@@ -1391,7 +1280,8 @@ hipError_t fft_batched_typed(int base, int mode, const void* tab, const unsigned
 
 hipError_t launch_batched_fft(int kind, const void* tab, const unsigned* st, int ns, unsigned nb, dim3 blk,
                               size_t lds, hipStream_t s) {
-    const int base = kind >> 8, mode = (kind >> 1) & 127, fp32 = kind & 1;
+    const int base = kind >> 12, mode = (kind >> 1) & 2047, fp32 = kind & 1;
+    if (base >= KK_SPLITXF) return launch_batched_split(kind, tab, st, ns, nb, blk, lds, s);
     return fp32 ? fft_batched_typed<float>(base, mode, tab, st, ns, nb, blk, lds, s)
                 : fft_batched_typed<double>(base, mode, tab, st, ns, nb, blk, lds, s);
 }

@@ -2353,7 +2353,7 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
 
 hipError_t launch_batched_stencil(int kind, const void* tab, const unsigned* st, int ns, unsigned nb, dim3 blk,
                                   size_t lds, hipStream_t s) {
-    const int base = kind >> 8, mode = (kind >> 1) & 127, fp32 = kind & 1;
+    const int base = kind >> 12, mode = (kind >> 1) & 2047, fp32 = kind & 1;
     if (base == KK_REFRES) {
         if (mode == 1) hipLaunchKernelGGL(k_refine_res_ib_b, dim3(nb), blk, 0, s, (const BRec<RefineResArgs>*)tab, st, ns);
         else hipLaunchKernelGGL(k_refine_res_b, dim3(nb), blk, 0, s, (const BRec<RefineResArgs>*)tab, st, ns);
