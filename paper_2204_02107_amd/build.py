@@ -16,15 +16,18 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdnslab.so")
-SOURCES = ["api.hip", "stencil.hip", "fft.hip", "fft_split.hip", "particles.hip", "postproc.hip"]
+SOURCES = ["api.hip", "stencil.hip", "fft.hip", "fft_split.hip", "fft_line.hip", "particles.hip", "postproc.hip"]
 ARCH = "gfx950"
 
-# Kernel instances of the three-pass FFT solve, one object per real type, pass
-# and range of the length tables (fft_split.h: 23 x and 19 z lengths).
-SPLIT_PARTS = [(f"split_{ax}{bits}_{h}", real, ax == "x", lo, hi)
-               for bits, real in ((64, "double"), (32, "float"))
-               for ax, cuts in (("x", (0, 8, 16, 23)), ("z", (0, 7, 13, 19)))
-               for h, (lo, hi) in enumerate(zip(cuts, cuts[1:]))]
+# Kernel instances of the FFT solves on register tiles, one object per real
+# type, pass and range of the length tables: fft_split.h (23 x and 19 z
+# lengths), fft_line.h (23 x lengths, 18 column lengths).
+PARTS = [(src, f"{name}_{ax}{bits}_{h}", real, ax == "x", lo, hi)
+         for src, name, axes in (("fft_split_part.hip", "split", (("x", (0, 8, 16, 23)), ("z", (0, 7, 13, 19)))),
+                                 ("fft_line_part.hip", "line", (("x", (0, 12, 23)), ("c", (0, 10, 18)))))
+         for bits, real in ((64, "double"), (32, "float"))
+         for ax, cuts in axes
+         for h, (lo, hi) in enumerate(zip(cuts, cuts[1:]))]
 
 # Packed FP32 instructions are disabled for all device code.
 HIPFLAGS = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}",
@@ -46,9 +49,9 @@ def build(verbose: bool = False) -> str:
     procs = []
     objs = []
     units = [(src, src.replace(".hip", ".o"), []) for src in SOURCES]
-    units += [("fft_split_part.hip", fn + ".o",
+    units += [(src, fn + ".o",
                [f"-DDNSLAB_PART_FN={fn}", f"-DDNSLAB_PART_T={real}", f"-DDNSLAB_PART_X={int(x)}",
-                f"-DDNSLAB_PART_LO={lo}", f"-DDNSLAB_PART_HI={hi}"]) for fn, real, x, lo, hi in SPLIT_PARTS]
+                f"-DDNSLAB_PART_LO={lo}", f"-DDNSLAB_PART_HI={hi}"]) for src, fn, real, x, lo, hi in PARTS]
     for src, o, defs in units:
         obj = os.path.join(BUILD, o)
         objs.append(obj)

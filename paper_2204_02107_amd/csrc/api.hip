@@ -16,6 +16,7 @@
 
 #include "common.h"
 #include "fft.h"
+#include "fft_line.h"
 #include "fft_split.h"
 #include "particles.h"
 #include "postproc.h"
@@ -102,6 +103,7 @@ struct Layout {
     int xtw_lds;          // x passes stage their twiddle tables in LDS
     int yz, lg_ca, lg_cb;  // fused plane pass (plane-major spectrum) and its LDS chunks
     AxisPlan px, py, pz;
+    LinePlan ln;           // axis-by-axis solve on register tiles (ln.on), where sp.r == 0
     SplitPlan sp;          // three-pass solve (sp.r > 0): the x passes carry a factor of the y transform
     StencilLaunch L;       // momentum and scalar stage kernels
     StencilLaunch L1;      // one-cell-per-thread kernels (div, refinement residual, rate)
@@ -362,6 +364,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
 #define DNSLAB_SPLIT 1
 #endif
     if (DNSLAB_SPLIT) Lo.sp = make_split_plan(P->nx, P->ny, P->nz, (int)Lo.esz);
+    if (Lo.sp.r == 0) Lo.ln = make_line_plan(P->nx, P->ny, P->nz);
     // Fused plane pass: each of the nx/2 + 1 kx planes (ny * nz values) held
     // by one block in registers, its y and z lines transformed in LDS chunks.
     // It cuts two of the three column passes and their launches, but one
@@ -372,7 +375,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     {
         const int nthr = yz_threads(P->ny, Lo.esz == 4);
         const long long max_plane = Lo.esz == 8 ? DNSLAB_YZ_MAX_PLANE : DNSLAB_YZ_MAX_PLANE32;
-        if (DNSLAB_YZ && Lo.sp.r == 0 && P->ny > 1 && P->nz > 1 && nthr > 0 && (long long)P->ny * P->nz <= max_plane &&
+        if (DNSLAB_YZ && Lo.sp.r == 0 && !Lo.ln.on && P->ny > 1 && P->nz > 1 && nthr > 0 && (long long)P->ny * P->nz <= max_plane &&
             yz_instance(Lo.esz == 4, nthr, (long long)P->ny * P->nz) >= 0 &&
             Lo.py.tpl <= nthr && Lo.pz.tpl <= nthr) {
             const size_t cap = (size_t)DNSLAB_YZ_LDS_KB * 1024;
@@ -651,6 +654,53 @@ SplitArgs<T> split_args_of(const Layout& Lo, const Grid& g, void* spec, const vo
     return a;
 }
 
+// The launches of the axis-by-axis solve (Lo.ln.on) through launch(kernel id,
+// issue): x, then the columns, then x back.
+template <typename T, class Launch>
+int line_solve(const Layout& Lo, const Grid& g, const FFTArgs<T>& f, const T* r, T* p, Launch&& launch) {
+    LineArgs<T> a = {};
+    a.spec = f.spec;
+    a.r = r;
+    a.p = p;
+    a.wx = f.wx;
+    a.tw = f.tw;
+    a.sx2 = f.sx2;
+    a.inv_ntot = f.inv_ntot;
+    a.nx = g.nx;
+    a.nlines = g.ny * g.nz;
+    a.rs = Lo.sx;
+    // columns along y of each z plane
+    LineArgs<T> y = a;
+    y.wc = f.wy;
+    y.sc2 = f.sy2;
+    y.sp2 = f.sz2;
+    y.rstr = a.rs;
+    y.pstr = g.ny * a.rs;
+    y.nplanes = g.nz;
+    int rc = launch(K_FXF, [&](hipStream_t s, Recorder* rec) { return launch_line_x<T>(a, Lo.ln.xi, false, s, rec); });
+    if (g.nz == 1) {
+        if (!rc) rc = launch(K_FY, [&](hipStream_t s, Recorder* rec) { return launch_line_cols<T>(y, Lo.ln.yi, 2, s, rec); });
+    } else {
+        // along z of each ky place
+        LineArgs<T> z = a;
+        const SplitDigits dy = line_digits(g.ny);
+        z.wc = f.wz;
+        z.sc2 = f.sz2;
+        z.sp2 = f.sy2;
+        z.rstr = g.ny * a.rs;
+        z.pstr = a.rs;
+        z.nplanes = g.ny;
+        z.d0 = dy.d[0];
+        z.d1 = dy.d[1];
+        z.np = dy.n;
+        if (!rc) rc = launch(K_FY, [&](hipStream_t s, Recorder* rec) { return launch_line_cols<T>(y, Lo.ln.yi, 0, s, rec); });
+        if (!rc) rc = launch(K_FZ, [&](hipStream_t s, Recorder* rec) { return launch_line_cols<T>(z, Lo.ln.zi, 2, s, rec); });
+        if (!rc) rc = launch(K_FY, [&](hipStream_t s, Recorder* rec) { return launch_line_cols<T>(y, Lo.ln.yi, 1, s, rec); });
+    }
+    if (!rc) rc = launch(K_FXI, [&](hipStream_t s, Recorder* rec) { return launch_line_x<T>(a, Lo.ln.xi, true, s, rec); });
+    return rc;
+}
+
 template <typename T>
 FFTArgs<T> fft_args(dnslab_ctx* x) {
     FFTArgs<T> a = fft_args_of<T>(x->Lo, x->g, x->spec, x->wx, x->sx2);
@@ -671,6 +721,11 @@ int poisson_solve(dnslab_ctx* x, const T* r, T* pout) {
         return DNSLAB_OK;
     }
     const FFTArgs<T> a = fft_args<T>(x);
+    if (x->Lo.ln.on)
+        return line_solve<T>(x->Lo, x->g, a, r, pout, [x](int kid, auto&& issue) -> int {
+            LAUNCH(x, kid, issue(x->cur, x->rec));
+            return DNSLAB_OK;
+        });
     LAUNCH(x, K_FXF, launch_fft_x_fwd<T>(a, r, x->cur, x->rec));
     if (x->Lo.yz) {
         LAUNCH(x, K_FYZ, launch_fft_yz_solve<T>(a, x->cur, x->rec));
@@ -1356,6 +1411,12 @@ int poisson_noalloc(const dnslab_params* P, const T* r, T* pout) {
         if (e != hipSuccess) return fail(nullptr, DNSLAB_EHIP, std::string("launch: ") + hipGetErrorString(e));
         return DNSLAB_OK;
     }
+    if (e == hipSuccess && Lo.ln.on)
+        return line_solve<T>(Lo, g, a, r, pout, [s](int, auto&& issue) -> int {
+            const hipError_t le = issue(s, nullptr);
+            if (le != hipSuccess) return fail(nullptr, DNSLAB_EHIP, std::string("launch: ") + hipGetErrorString(le));
+            return DNSLAB_OK;
+        });
     if (e == hipSuccess) e = launch_fft_x_fwd<T>(a, r, s);
     if (e == hipSuccess) {
         if (Lo.yz) {

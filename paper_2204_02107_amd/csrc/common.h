@@ -147,6 +147,7 @@ enum KernelKind : int {
     KK_MOMPAIR, KK_SCAPAIR,
     KK_IB = 32, KK_FXF, KK_FXI, KK_COLS,                                              // fft.hip
     KK_SPLITXF, KK_SPLITXI, KK_SPLITZ,                                                // fft_split.hip
+    KK_LINEXF, KK_LINEXI, KK_LINEC,                                                   // fft_line.hip
 };
 __host__ __device__ constexpr int kind_code(int base, int mode, int fp32) { return (base << 12) | (mode << 1) | fp32; }
 

@@ -18,6 +18,7 @@
 // with one block per kx plane.
 #include "fft.h"
 #include "fft_dev.h"
+#include "fft_line.h"
 #include "fft_split.h"
 
 #include <algorithm>
@@ -1281,6 +1282,7 @@ hipError_t fft_batched_typed(int base, int mode, const void* tab, const unsigned
 hipError_t launch_batched_fft(int kind, const void* tab, const unsigned* st, int ns, unsigned nb, dim3 blk,
                               size_t lds, hipStream_t s) {
     const int base = kind >> 12, mode = (kind >> 1) & 2047, fp32 = kind & 1;
+    if (base >= KK_LINEXF) return launch_batched_line(kind, tab, st, ns, nb, blk, lds, s);
     if (base >= KK_SPLITXF) return launch_batched_split(kind, tab, st, ns, nb, blk, lds, s);
     return fp32 ? fft_batched_typed<float>(base, mode, tab, st, ns, nb, blk, lds, s)
                 : fft_batched_typed<double>(base, mode, tab, st, ns, nb, blk, lds, s);

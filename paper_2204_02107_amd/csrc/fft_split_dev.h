@@ -195,8 +195,8 @@ struct XG {
 
 // Transform of a digit (stride S in blocks of L places) of every unit, with
 // its twiddles W_L^{k j} after (forward) or before (inverse) it.
-template <class X, int M, int S, bool INV, typename T, int U, int D>
-__device__ __forceinline__ void x_digit(C2<T> (&v)[U][D], const C2<T>* W, int tid) {
+template <class X, int M, int S, bool INV, class Tab, typename T, int U, int D>
+__device__ __forceinline__ void x_digit(C2<T> (&v)[U][D], const Tab& W, int tid) {
     constexpr int L = D * S;
 #pragma unroll
     for (int i = 0; i < U; ++i) {

@@ -34,6 +34,7 @@ SplitKernel<T> pick_length(int i, int j, bool inverse) {
 }  // namespace
 
 SplitKernel<DNSLAB_PART_T> DNSLAB_PART_FN(int i, int j, bool inverse) {
+    if (i < DNSLAB_PART_LO) return nullptr;
     return pick_length<DNSLAB_PART_T, DNSLAB_PART_LO>(i, j, inverse);
 }
 

@@ -1,5 +1,6 @@
-"""The three-pass FFT solve (the y transform split between the x passes and the
-z pass) against the oracle's Poisson solve (Section 2.2).
+"""The FFT solves on register tiles against the oracle's Poisson solve (Section
+2.2): the three-pass solve (the y transform split between the x passes and the
+z pass) and the axis-by-axis one.
 
 The shapes (nz, ny, nx) take every compiled x length nx/2, every factor pair
 (R, Q) of ny and every z length once or more, with cells of unequal sides, in
@@ -26,12 +27,21 @@ SHAPES = [(16, 24, 32), (24, 32, 48), (32, 96, 64), (36, 128, 72), (48, 144, 96)
           (24, 32, 972), (24, 243, 48), (2, 32, 48)]
 
 
+# The axis-by-axis solve: every x length and column length of its tables, 2D
+# (nz = 1, one column pass) and 3D with y transforms too long to be split.
+LINE_SHAPES = [(1, 54, 324), (1, 64, 384), (1, 72, 432), (1, 81, 486), (1, 96, 512), (1, 108, 576), (1, 128, 648),
+               (1, 144, 768), (1, 162, 864), (1, 192, 972), (1, 216, 1024), (1, 243, 1152), (1, 256, 1296),
+               (1, 288, 1458), (1, 324, 1536), (1, 384, 1728), (1, 432, 1944), (1, 512, 2048), (1, 54, 2304),
+               (1, 64, 2592), (1, 54, 2916), (1, 64, 3072), (1, 54, 3456),
+               (54, 288, 324), (64, 512, 384), (81, 324, 432), (96, 432, 512), (243, 54, 972), (128, 384, 324)]
+
+
 @pytest.mark.parametrize("form", ["fp64", "fp32"])
-@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("shape", SHAPES + LINE_SHAPES)
 def test_split_solve(shape, form):
     torch, m = need_gpu()
     sc = case(shape, 3)
-    announce(f"three-pass solve {form} shape={shape}")
+    announce(f"register-tile solve {form} shape={shape}")
     S = m.Solver(sc, precision=m.FP64 if form == "fp64" else m.FP32_REFINE)
     r = np.random.default_rng(33).standard_normal(shape)
     got = to_np(S.poisson(r))
