@@ -130,6 +130,18 @@ struct BRec {
     unsigned g[3];
 };
 
+// Pointers of an argument record in the batched table, read as pointers to
+// global memory: the compiler cannot see that of a plain pointer loaded from
+// memory and would use flat accesses, which go through the aperture check and
+// count with the LDS operations, so that every wait for LDS also waits for them.
+template <class P>
+__device__ __forceinline__ P* global_field(P* const& f) {
+    return (P*)*(__attribute__((address_space(1))) P* const*)&f;
+}
+#define DNSLAB_G(f) a.f = global_field(t.f)
+#define DNSLAB_G3(f) DNSLAB_G(f[0]), DNSLAB_G(f[1]), DNSLAB_G(f[2])
+#define DNSLAB_GFORCE DNSLAB_G(frc.idx), DNSLAB_G(frc.S), DNSLAB_G(frc.uset), DNSLAB_G(frc.cset)
+
 // Scenario of this block in a batched launch: starts[s] <= blockIdx.x < starts[s+1].
 __device__ __forceinline__ int batch_slot(const unsigned* __restrict__ starts, int ns) {
     int lo = 0, hi = ns - 1;

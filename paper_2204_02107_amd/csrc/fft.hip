@@ -974,7 +974,9 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_ib_rhs_b(const BRec<IbArgs<T>>* __restrict__ tab,
                                                   const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_BLOCK(st, ns)
-    const IbArgs<T> a = tab[s_].a;
+    const IbArgs<T>& t = tab[s_].a;
+    IbArgs<T> a = t;
+    DNSLAB_G(ib.idx), DNSLAB_G(ib.mask), DNSLAB_G(p), DNSLAB_G(r), DNSLAB_G(r0s);
     ib_rhs_body<T>(a, blk_);
 }
 template <typename T>

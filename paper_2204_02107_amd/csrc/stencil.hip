@@ -1894,13 +1894,80 @@ __global__ __launch_bounds__(1024) void k_set_rate(PartSoA part, int np, StepSca
     bi_.gy = tab[s_].g[1];                              \
     bi_.gz = tab[s_].g[2];
 
+// An argument record of the batched table (t) with its pointers global.
+template <typename T>
+__device__ __forceinline__ MomArgs<T> from_table(const MomArgs<T>& t) {
+    MomArgs<T> a = t;
+    DNSLAB_G3(us), DNSLAB_G3(un), DNSLAB_G3(acc), DNSLAB_G3(out), DNSLAB_G(flags), DNSLAB_G(dtp), DNSLAB_GFORCE;
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ MomPairArgs<T> from_table(const MomPairArgs<T>& t) {
+    MomPairArgs<T> a = t;
+    DNSLAB_G3(vin), DNSLAB_G3(un), DNSLAB_G3(accin), DNSLAB_G3(acc), DNSLAB_G3(out), DNSLAB_G(flags), DNSLAB_G(dtp),
+        DNSLAB_GFORCE;
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ ScaArgs<T> from_table(const ScaArgs<T>& t) {
+    ScaArgs<T> a = t;
+    DNSLAB_G3(u), DNSLAB_G(cs), DNSLAB_G(cn), DNSLAB_G(acc), DNSLAB_G(out), DNSLAB_G(flags), DNSLAB_G(dtp),
+        DNSLAB_G(part.p), DNSLAB_GFORCE;
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ ScaPairArgs<T> from_table(const ScaPairArgs<T>& t) {
+    ScaPairArgs<T> a = t;
+    DNSLAB_G3(u), DNSLAB_G(cin), DNSLAB_G(cn), DNSLAB_G(accin), DNSLAB_G(acc), DNSLAB_G(out), DNSLAB_G(flags),
+        DNSLAB_G(dtp), DNSLAB_G(part.p), DNSLAB_GFORCE;
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ FiltArgs<T> from_table(const FiltArgs<T>& t) {
+    FiltArgs<T> a = t;
+    DNSLAB_G3(in), DNSLAB_G3(out), DNSLAB_G(flags), DNSLAB_G(part.p);
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ CorrArgs<T> from_table(const CorrArgs<T>& t) {
+    CorrArgs<T> a = t;
+    DNSLAB_G3(us), DNSLAB_G3(out), DNSLAB_G(p), DNSLAB_G(flags), DNSLAB_G(part.p);
+    return a;
+}
+template <typename T>
+__device__ __forceinline__ DivArgs<T> from_table(const DivArgs<T>& t) {
+    DivArgs<T> a = t;
+    DNSLAB_G3(u), DNSLAB_G(out);
+    return a;
+}
+__device__ __forceinline__ RefineResArgs from_table(const RefineResArgs& t) {
+    RefineResArgs a = t;
+    DNSLAB_G3(us), DNSLAB_G(p3), DNSLAB_G(p4), DNSLAB_G(flags), DNSLAB_G(res), DNSLAB_G(ib.idx), DNSLAB_G(ib.mask);
+    return a;
+}
+__device__ __forceinline__ RefineCorrArgs from_table(const RefineCorrArgs& t) {
+    RefineCorrArgs a = t;
+    DNSLAB_G3(us), DNSLAB_G3(out), DNSLAB_G(p4), DNSLAB_G(dp), DNSLAB_G(p), DNSLAB_G(flags), DNSLAB_G(part.p);
+    return a;
+}
+__device__ __forceinline__ AdvanceArgs from_table(const AdvanceArgs& t) {
+    AdvanceArgs a = t;
+    DNSLAB_G(part.p), DNSLAB_G(sc);
+    return a;
+}
+__device__ __forceinline__ DiagArgs from_table(const DiagArgs& t) {
+    DiagArgs a = t;
+    DNSLAB_G(part.p), DNSLAB_G(sc), DNSLAB_G(ring);
+    return a;
+}
+
 template <typename T, int MODE, bool LDS>
 __global__ __launch_bounds__(1024) void k_mom_stage(const MomArgs<T> a) { mom_stage_body<T, MODE, LDS>(a, hw_block()); }
 template <typename T, int MODE, bool LDS>
 __global__ __launch_bounds__(1024) void k_mom_stage_b(const BRec<MomArgs<T>>* __restrict__ tab,
                                                       const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const MomArgs<T> a = tab[s_].a;
+    const MomArgs<T> a = from_table(tab[s_].a);
     mom_stage_body<T, MODE, LDS>(a, bi_);
 }
 template <typename T, int PAIR>
@@ -1911,7 +1978,7 @@ template <typename T, int PAIR>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, true, PAIR>()))) void k_mom_pair_b(const BRec<MomPairArgs<T>>* __restrict__ tab,
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const MomPairArgs<T> a = tab[s_].a;
+    const MomPairArgs<T> a = from_table(tab[s_].a);
     mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS>(a, bi_);
 }
 template <typename T, int PAIR>
@@ -1922,7 +1989,7 @@ template <typename T, int PAIR>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, false, PAIR>()))) void k_sca_pair_b(const BRec<ScaPairArgs<T>>* __restrict__ tab,
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const ScaPairArgs<T> a = tab[s_].a;
+    const ScaPairArgs<T> a = from_table(tab[s_].a);
     sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS>(a, bi_);
 }
 template <typename T, int MODE>
@@ -1931,7 +1998,7 @@ template <typename T, int MODE>
 __global__ __launch_bounds__(1024) void k_sca_stage_b(const BRec<ScaArgs<T>>* __restrict__ tab,
                                                       const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const ScaArgs<T> a = tab[s_].a;
+    const ScaArgs<T> a = from_table(tab[s_].a);
     sca_stage_body<T, MODE>(a, bi_);
 }
 template <typename T, int NF>
@@ -1940,7 +2007,7 @@ template <typename T, int NF>
 __global__ __launch_bounds__(1024) void k_filter_b(const BRec<FiltArgs<T>>* __restrict__ tab,
                                                    const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const FiltArgs<T> a = tab[s_].a;
+    const FiltArgs<T> a = from_table(tab[s_].a);
     filter_body<T, NF>(a, bi_);
 }
 template <typename T, int NF>
@@ -1949,7 +2016,7 @@ template <typename T, int NF>
 __global__ __launch_bounds__(1024) void k_filter_lds_b(const BRec<FiltArgs<T>>* __restrict__ tab,
                                                        const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const FiltArgs<T> a = tab[s_].a;
+    const FiltArgs<T> a = from_table(tab[s_].a);
     filter_lds_body<T, NF>(a, bi_);
 }
 template <typename T, int NF>
@@ -1960,7 +2027,7 @@ template <typename T, int NF>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_filter_ring_b(const BRec<FiltArgs<T>>* __restrict__ tab,
                                                        const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const FiltArgs<T> a = tab[s_].a;
+    const FiltArgs<T> a = from_table(tab[s_].a);
     filter_ring_body<T, NF, DNSLAB_FROWS>(a, bi_);
 }
 template <typename T>
@@ -1969,7 +2036,7 @@ template <typename T>
 __global__ __launch_bounds__(1024) void k_correct_b(const BRec<CorrArgs<T>>* __restrict__ tab,
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const CorrArgs<T> a = tab[s_].a;
+    const CorrArgs<T> a = from_table(tab[s_].a);
     correct_body<T>(a, bi_);
 }
 template <typename T>
@@ -1978,21 +2045,21 @@ template <typename T>
 __global__ __launch_bounds__(1024) void k_div_b(const BRec<DivArgs<T>>* __restrict__ tab,
                                                 const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const DivArgs<T> a = tab[s_].a;
+    const DivArgs<T> a = from_table(tab[s_].a);
     div_body<T>(a, bi_);
 }
 __global__ __launch_bounds__(1024) void k_refine_res(const RefineResArgs a) { refine_res_body(a, hw_block()); }
 __global__ __launch_bounds__(1024) void k_refine_res_b(const BRec<RefineResArgs>* __restrict__ tab,
                                                        const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const RefineResArgs a = tab[s_].a;
+    const RefineResArgs a = from_table(tab[s_].a);
     refine_res_body(a, bi_);
 }
 __global__ __launch_bounds__(256) void k_refine_res_ib(const RefineResArgs a) { refine_res_ib_body(a, blockIdx.x); }
 __global__ __launch_bounds__(256) void k_refine_res_ib_b(const BRec<RefineResArgs>* __restrict__ tab,
                                                          const unsigned* __restrict__ st, int ns) {
     const int s_ = batch_slot(st, ns);
-    const RefineResArgs a = tab[s_].a;
+    const RefineResArgs a = from_table(tab[s_].a);
     refine_res_ib_body(a, blockIdx.x - st[s_]);
 }
 template <typename T>
@@ -2013,7 +2080,7 @@ template <typename T>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_correct_ring_b(const BRec<CorrArgs<T>>* __restrict__ tab,
                                                         const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const CorrArgs<T> a = tab[s_].a;
+    const CorrArgs<T> a = from_table(tab[s_].a);
     correct_ring<T>(a, bi_);
 }
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_refine_correct_ring(const RefineCorrArgs a) {
@@ -2022,7 +2089,7 @@ __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_refine_correct_ring(const
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_refine_correct_ring_b(const BRec<RefineCorrArgs>* __restrict__ tab,
                                                                const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const RefineCorrArgs a = tab[s_].a;
+    const RefineCorrArgs a = from_table(tab[s_].a);
     refine_correct_ring(a, bi_);
 }
 __global__ __launch_bounds__(1024) void k_refine_correct(const RefineCorrArgs a) {
@@ -2031,7 +2098,7 @@ __global__ __launch_bounds__(1024) void k_refine_correct(const RefineCorrArgs a)
 __global__ __launch_bounds__(1024) void k_refine_correct_b(const BRec<RefineCorrArgs>* __restrict__ tab,
                                                            const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
-    const RefineCorrArgs a = tab[s_].a;
+    const RefineCorrArgs a = from_table(tab[s_].a);
     refine_correct_body(a, bi_);
 }
 __global__ __launch_bounds__(1024) void k_advance(const AdvanceArgs a) { advance_body(a); }
@@ -2039,7 +2106,7 @@ __global__ __launch_bounds__(1024) void k_advance_b(const BRec<AdvanceArgs>* __r
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
     (void)bi_;
-    const AdvanceArgs a = tab[s_].a;
+    const AdvanceArgs a = from_table(tab[s_].a);
     advance_body(a);
 }
 __global__ __launch_bounds__(1024) void k_diag(const DiagArgs a) { diag_body(a); }
@@ -2047,7 +2114,7 @@ __global__ __launch_bounds__(1024) void k_diag_b(const BRec<DiagArgs>* __restric
                                                  const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
     (void)bi_;
-    const DiagArgs a = tab[s_].a;
+    const DiagArgs a = from_table(tab[s_].a);
     diag_body(a);
 }
 
