@@ -293,13 +293,31 @@ Grid make_grid(const dnslab_params* P) {
 #define DNSLAB_PKC_LONG_BLOCKS32 4096
 #endif
 
-// z chunk: enough blocks to fill the chip, each walking at least 4 planes.
-int stencil_kc(const Grid& g, int rows, int forced) {
+// Grids below DNSLAB_SMALL_CELLS leave most CUs idle with the usual chunks and
+// are bound by the length of a block's march: radius-1 stencils then take one
+// plane per block, the filter 64 x 4 tiles and 4 planes (DNSLAB_FILTER_SMALL_CELLS).
+// Measured per step, FP64 / FP32: 64^3 188 -> 157 / 200 -> 169 us, 128x64x64
+// 222 -> 189 / 214 -> 194; 192x96x64 FP32 284 -> 274 (filter 28 -> 20 us, its
+// radius-1 stencils one plane faster in FP32 alone, 2 planes there); one plane
+// on 256x128x96 was slower (650 -> 662, 470 -> 483), two in FP32 faster
+// (460).
+#ifndef DNSLAB_SMALL_CELLS
+#define DNSLAB_SMALL_CELLS (1LL << 19)
+#endif
+#ifndef DNSLAB_SMALL_CELLS32
+#define DNSLAB_SMALL_CELLS32 (1LL << 22)   // FP32: two planes up to this
+#endif
+#ifndef DNSLAB_FILTER_SMALL_CELLS
+#define DNSLAB_FILTER_SMALL_CELLS (1LL << 21)
+#endif
+
+// z chunk: enough blocks to fill the chip, each walking at least kc_min planes.
+int stencil_kc(const Grid& g, int rows, int forced, int kc_min = 4) {
     if (forced > 0) return std::min(forced, g.nz);
     const StencilLaunch one = stencil_launch(g, rows, g.nz, 1);
     const long long cols = (long long)one.grid.x * one.grid.y;
     long long kc = (long long)g.nz * cols / 4096;
-    kc = std::max(4LL, std::min(32LL, kc));
+    kc = std::max<long long>(kc_min, std::min(32LL, kc));
     return (int)std::min<long long>(kc, g.nz);
 }
 
@@ -395,7 +413,8 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
             }
         }
     }
-    Lo.L = stencil_launch(g, DNSLAB_ROWS, stencil_kc(g, DNSLAB_ROWS, DNSLAB_KC), 1);
+    const int kc_min = g.n <= DNSLAB_SMALL_CELLS ? 1 : Lo.esz == 4 && g.n <= DNSLAB_SMALL_CELLS32 ? 2 : 4;
+    Lo.L = stencil_launch(g, DNSLAB_ROWS, stencil_kc(g, DNSLAB_ROWS, DNSLAB_KC, kc_min), 1);
     Lo.L1 = Lo.L;
     // Filter and correction: 64 x DNSLAB_FROWS tiles with long z chunks (the
     // radius-3 filter re-reads 6 halo planes per chunk), their register-ring
@@ -414,7 +433,10 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     }
     if (!ring_geometry) {
         const int small_min = Lo.esz == 8 ? DNSLAB_FKC_MIN_SMALL : DNSLAB_FKC_MIN_SMALL32;
-        Lo.LF = stencil_launch(g, 8, std::max(stencil_kc(g, 8, DNSLAB_FKC), std::min(small_min, P->nz)), 1);
+        if (g.n < DNSLAB_FILTER_SMALL_CELLS)
+            Lo.LF = stencil_launch(g, 4, std::min(4, P->nz), 1);
+        else
+            Lo.LF = stencil_launch(g, 8, std::max(stencil_kc(g, 8, DNSLAB_FKC), std::min(small_min, P->nz)), 1);
     }
     {
         // the pair kernels read kc + 4 planes and evaluate their first stage on
@@ -438,7 +460,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     Lo.off_flags = take((size_t)g.n);
     Lo.nfields = P->filter ? 16 : 13;
     Lo.off_fields = take((size_t)Lo.nfields * g.n * Lo.esz);
-    Lo.off_spec = take((size_t)Lo.sx * nlines * csz);
+    Lo.off_spec = take((Lo.sp.r > 0 ? (size_t)Lo.sp.gs * Lo.sp.q * P->nz : (size_t)Lo.sx * nlines) * csz);
     Lo.off_tw = take((size_t)(Lo.m + P->ny + P->nz + Lo.m + 1) * csz);
     Lo.off_s2 = take((size_t)(Lo.m + 1 + P->ny + P->nz) * sizeof(double));
     Lo.nforced_cap = std::max(1, n_forced);
