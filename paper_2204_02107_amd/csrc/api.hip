@@ -110,10 +110,12 @@ struct Layout {
     StencilLaunch LC;      // the velocity correction (64 x DNSLAB_FROWS tiles: its register-ring form)
     StencilLaunch LF;      // filter
     StencilLaunch LP;      // fused RK4 stage pairs
+    int need;              // iterates that only the immersed-boundary term reads are written there only
+    int seg_lg;            // cells per segment of the words of cells the immersed-boundary term reads
     int nparts;            // partial-result slots (max block count of the reducing kernels)
     int nfields;           // work fields: 13, plus 3 for the projected velocity when the filter is on
     // byte offsets inside the workspace
-    size_t off_flags, off_fields, off_spec, off_tw, off_s2, off_forced, off_part, off_sc, off_ring;
+    size_t off_flags, off_fields, off_spec, off_need, off_tw, off_s2, off_forced, off_part, off_sc, off_ring;
     size_t total;
     int nforced_cap;
 };
@@ -311,6 +313,10 @@ Grid make_grid(const dnslab_params* P) {
 #define DNSLAB_FILTER_SMALL_CELLS (1LL << 21)
 #endif
 
+#ifndef DNSLAB_IB_ONLY_CELLS
+#define DNSLAB_IB_ONLY_CELLS (1LL << 23)   // see poisson_solve
+#endif
+
 // z chunk: enough blocks to fill the chip, each walking at least kc_min planes.
 int stencil_kc(const Grid& g, int rows, int forced, int kc_min = 4) {
     if (forced > 0) return std::min(forced, g.nz);
@@ -461,6 +467,10 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     Lo.nfields = P->filter ? 16 : 13;
     Lo.off_fields = take((size_t)Lo.nfields * g.n * Lo.esz);
     Lo.off_spec = take((Lo.sp.r > 0 ? (size_t)Lo.sp.gs * Lo.sp.q * P->nz : (size_t)Lo.sx * nlines) * csz);
+    Lo.need = (Lo.sp.r > 0 || Lo.ln.on) && g.n >= DNSLAB_IB_ONLY_CELLS;
+    Lo.off_need = take(Lo.need ? (size_t)nlines * sizeof(unsigned long long) : 0);
+    Lo.seg_lg = 4;                                  // 16-cell segments, at most 64 of them per line
+    while ((P->nx - 1) >> Lo.seg_lg >= 64) ++Lo.seg_lg;
     Lo.off_tw = take((size_t)(Lo.m + P->ny + P->nz + Lo.m + 1) * csz);
     Lo.off_s2 = take((size_t)(Lo.m + 1 + P->ny + P->nz) * sizeof(double));
     Lo.nforced_cap = std::max(1, n_forced);
@@ -517,6 +527,7 @@ struct dnslab_ctx {
     bool any_solid;
     void* ib_buf;          // near-solid list: idx (int), mask (uint8), saved r0 (field type)
     void* ib_r0;
+    unsigned long long* need;   // per x line: the segments that the immersed-boundary term reads p in
     IBList ib;
     bool rate_valid;
     long long host_step;
@@ -679,7 +690,8 @@ SplitArgs<T> split_args_of(const Layout& Lo, const Grid& g, void* spec, const vo
 // The launches of the axis-by-axis solve (Lo.ln.on) through launch(kernel id,
 // issue): x, then the columns, then x back.
 template <typename T, class Launch>
-int line_solve(const Layout& Lo, const Grid& g, const FFTArgs<T>& f, const T* r, T* p, Launch&& launch) {
+int line_solve(const Layout& Lo, const Grid& g, const FFTArgs<T>& f, const T* r, T* p,
+               const unsigned long long* need, Launch&& launch) {
     LineArgs<T> a = {};
     a.spec = f.spec;
     a.r = r;
@@ -688,6 +700,8 @@ int line_solve(const Layout& Lo, const Grid& g, const FFTArgs<T>& f, const T* r,
     a.tw = f.tw;
     a.sx2 = f.sx2;
     a.inv_ntot = f.inv_ntot;
+    a.need = need;
+    a.seg_lg = Lo.seg_lg;
     a.nx = g.nx;
     a.nlines = g.ny * g.nz;
     a.rs = Lo.sx;
@@ -731,12 +745,20 @@ FFTArgs<T> fft_args(dnslab_ctx* x) {
 }
 
 // One FFT solve of Lap p = r (central-difference symbol, null modes zero).
+// ib_only: p is an iterate that only the immersed-boundary term of the next one
+// reads, at the cells next to a solid and two cells beyond: the x inverse
+// leaves the other segments unwritten on grids from DNSLAB_IB_ONLY_CELLS
+// (1024x512x256 FP64 x inverse 405 -> 290 us; on 256x128x96, where walls are near
+// everywhere and the pass is not bound by its stores, 17.0 -> 18.4).
 template <typename T>
-int poisson_solve(dnslab_ctx* x, const T* r, T* pout) {
+int poisson_solve(dnslab_ctx* x, const T* r, T* pout, bool ib_only = false) {
+    const unsigned long long* need = ib_only ? x->need : nullptr;
     if (x->Lo.sp.r > 0) {
         SplitArgs<T> b = split_args_of<T>(x->Lo, x->g, x->spec, x->wx, x->sx2);
         b.r = r;
         b.p = pout;
+        b.need = need;
+        b.seg_lg = x->Lo.seg_lg;
         LAUNCH(x, K_FXF, launch_split_x<T>(b, x->Lo.sp, false, x->cur, x->rec));
         LAUNCH(x, K_FYZ, launch_split_z<T>(b, x->Lo.sp, x->cur, x->rec));
         LAUNCH(x, K_FXI, launch_split_x<T>(b, x->Lo.sp, true, x->cur, x->rec));
@@ -744,7 +766,7 @@ int poisson_solve(dnslab_ctx* x, const T* r, T* pout) {
     }
     const FFTArgs<T> a = fft_args<T>(x);
     if (x->Lo.ln.on)
-        return line_solve<T>(x->Lo, x->g, a, r, pout, [x](int kid, auto&& issue) -> int {
+        return line_solve<T>(x->Lo, x->g, a, r, pout, need, [x](int kid, auto&& issue) -> int {
             LAUNCH(x, kid, issue(x->cur, x->rec));
             return DNSLAB_OK;
         });
@@ -792,7 +814,7 @@ int project_solve(dnslab_ctx* x, const T* const us[3], void* const* scr = nullpt
     T* p_last = refine ? (T*)S[0] : p;    // the last iterate goes to a scratch field when refining
     for (int it = 0; it < nit; ++it) {
         if (x->any_solid) LAUNCH(x, K_IB, launch_ib_rhs<T>(x->ib, x->g, p, r0, (T*)x->ib_r0, it == 0, x->cur, x->rec));
-        int rc = poisson_solve<T>(x, r0, it == nit - 1 ? p_last : p);
+        int rc = poisson_solve<T>(x, r0, it == nit - 1 ? p_last : p, it < nit - 1);
         if (rc) return rc;
     }
     if constexpr (sizeof(T) == 4) {
@@ -1231,6 +1253,10 @@ int build_flags(dnslab_ctx* x, const uint8_t* beta_dev, const long long* fidx_ho
         x->ib_r0 = b + b_idx + b_mask;
     }
     x->ib.n = (int)nib;
+    if (any_solid && x->Lo.need) {
+        x->need = (unsigned long long*)((char*)x->ws + x->Lo.off_need);
+        HIPCHK(x, launch_ib_need(x->ib, g, x->Lo.seg_lg, x->need, x->stream));
+    }
     return DNSLAB_OK;
 }
 
@@ -1434,7 +1460,7 @@ int poisson_noalloc(const dnslab_params* P, const T* r, T* pout) {
         return DNSLAB_OK;
     }
     if (e == hipSuccess && Lo.ln.on)
-        return line_solve<T>(Lo, g, a, r, pout, [s](int, auto&& issue) -> int {
+        return line_solve<T>(Lo, g, a, r, pout, nullptr, [s](int, auto&& issue) -> int {
             const hipError_t le = issue(s, nullptr);
             if (le != hipSuccess) return fail(nullptr, DNSLAB_EHIP, std::string("launch: ") + hipGetErrorString(le));
             return DNSLAB_OK;

@@ -115,6 +115,11 @@ template <typename T>
 hipError_t launch_ib_rhs(const IBList& ib, const Grid& g, const T* p, T* r, T* r0s, int first, hipStream_t s,
                          Recorder* rec = nullptr);
 
+// need[line] bit (i >> seg_lg): the immersed-boundary term of some listed cell
+// reads p in that segment of the line (the cell itself and, where its mask says
+// solid, the cell two further).  Clears the ny nz words first.
+hipError_t launch_ib_need(const IBList& ib, const Grid& g, int seg_lg, unsigned long long* need, hipStream_t s);
+
 // Forward x pass: real-to-complex along x of r into the spectrum.
 template <typename T>
 hipError_t launch_fft_x_fwd(const FFTArgs<T>& a, const T* r, hipStream_t s, Recorder* rec = nullptr);

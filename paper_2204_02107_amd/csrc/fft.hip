@@ -979,6 +979,30 @@ __global__ __launch_bounds__(256) void k_ib_rhs_b(const BRec<IbArgs<T>>* __restr
     DNSLAB_G(ib.idx), DNSLAB_G(ib.mask), DNSLAB_G(p), DNSLAB_G(r), DNSLAB_G(r0s);
     ib_rhs_body<T>(a, blk_);
 }
+__global__ __launch_bounds__(256) void k_clear_words(unsigned long long* __restrict__ w, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) w[i] = 0;
+}
+__global__ __launch_bounds__(256) void k_ib_need(const IBList ib, const Grid g, int seg_lg,
+                                                 unsigned long long* __restrict__ need) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= ib.n) return;
+    const unsigned id = (unsigned)ib.idx[e], mk = ib.mask[e];
+    const unsigned nx = g.nx, ny = g.ny, nz = g.nz;
+    const unsigned i = id % nx, jk = id / nx, j = jk % ny, k = jk / ny;
+    auto mark = [&](unsigned ii, unsigned jj, unsigned kk) {
+        unsigned long long* w = need + (jj + ny * kk);
+        const unsigned long long bit = 1ull << (ii >> seg_lg);
+        if (!(*(volatile unsigned long long*)w & bit)) atomicOr(w, bit);
+    };
+    mark(i, j, k);
+    if (mk & 1u) mark((i + 2) % nx, j, k);
+    if (mk & 2u) mark((i + 2 * nx - 2) % nx, j, k);
+    if (mk & 4u) mark(i, (j + 2) % ny, k);
+    if (mk & 8u) mark(i, (j + 2 * ny - 2) % ny, k);
+    if (mk & 16u) mark(i, j, (k + 2) % nz);
+    if (mk & 32u) mark(i, j, (k + 2 * nz - 2) % nz);
+}
 template <typename T>
 __global__ __launch_bounds__(1024) void k_fft_x_fwd(const FxfArgs<T> a) { fft_x_fwd_body<T>(a, blockIdx.x); }
 template <typename T>
@@ -1116,6 +1140,13 @@ hipError_t launch_ib_rhs(const IBList& ib, const Grid& g, const T* p, T* r, T* r
         return hipSuccess;
     }
     hipLaunchKernelGGL((k_ib_rhs<T>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_ib_need(const IBList& ib, const Grid& g, int seg_lg, unsigned long long* need, hipStream_t s) {
+    const int nl = g.ny * g.nz;
+    hipLaunchKernelGGL(k_clear_words, dim3((nl + 255) / 256), dim3(256), 0, s, need, nl);
+    if (ib.n > 0) hipLaunchKernelGGL(k_ib_need, dim3((ib.n + 255) / 256), dim3(256), 0, s, ib, g, seg_lg, need);
     return hipGetLastError();
 }
 

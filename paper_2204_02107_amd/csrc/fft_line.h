@@ -29,6 +29,8 @@ struct LineArgs {
     const double* sc2;
     const double* sp2;
     double inv_ntot;
+    const unsigned long long* need;   // as SplitArgs::need
+    int seg_lg;
     int nx;
     int nlines;         // x passes: lines
     int rs;             // row stride

@@ -216,8 +216,10 @@ __global__ __launch_bounds__(line_x_geom(M, (int)sizeof(T)).nt) void k_line_x_in
         const int u = tid + i * NT, l = u % X::NL, line = (int)blk * X::NL + l;
         const unsigned o = (unsigned)line * M + (unsigned)(u / X::NL);
         if (u < X::F0::N && line < a.nlines) {
+            const unsigned long long need = a.need ? need_word(a.need, line) : ~0ull;
 #pragma unroll
-            for (int r = 0; r < X::D0; ++r) stg(dst + r * X::S0, o, v1[i][r]);
+            for (int r = 0; r < X::D0; ++r)
+                if (need >> ((unsigned)(2 * (u / X::NL + r * X::S0)) >> a.seg_lg) & 1u) stg(dst + r * X::S0, o, v1[i][r]);
         }
     }
 }

@@ -25,6 +25,11 @@ struct SplitArgs {
     const double* sz2;
     double inv_ntot;
     int nx, ny, nz;
+    // x inverse of an iterate that only the immersed-boundary term reads: one
+    // word per line, bit (i >> seg_lg) set where cells of that segment are read;
+    // the others are not written (NULL: everything is)
+    const unsigned long long* need;
+    int seg_lg;
     int q;              // Q = ny / R
     int gs;             // stride of a group of R rows of the spectrum
 };

@@ -86,6 +86,10 @@ __device__ __forceinline__ double ldg(const double* base, unsigned i) {
     return ((const __attribute__((address_space(1))) double*)base)[i];
 }
 
+__device__ __forceinline__ unsigned long long need_word(const unsigned long long* need, int line) {
+    return ((const __attribute__((address_space(1))) unsigned long long*)need)[line];
+}
+
 // Barrier between LDS stages that waits for the wave's LDS operations only:
 // global loads of the next tile and stores of the last one stay in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -379,16 +383,24 @@ __global__ __launch_bounds__(split_x_threads(M)) void k_split_x_inv(SplitArgs<T>
     exchange_stages<X::HALF, NT, typename X::F1, typename X::F0>(s, v2, v1, tid, X::f1, X::f0);
     x_digit<X, M, X::S0, true>(v1, W, tid);
     exchange_stages<X::HALF, NT, typename X::F0, typename X::Io>(s, v1, v0, tid, X::f0, X::io);
-    const int g0 = tid / M, n0 = tid % M, grp0 = (int)blk * X::G + g0;
+    const int g0 = X::G == 1 ? 0 : tid / M, n0 = tid - g0 * M, grp0 = (int)blk * X::G + g0;
     if (tid < X::Io::N && grp0 < ngrp) {
 #pragma unroll
         for (int r = 1; r < R; ++r) v0[0][r] = cmulc(v0[0][r], wy[g0 * R + r]);
         DFT<T, R, true>::run(v0[0]);
         const int z = grp0 / Q, q = grp0 - z * Q;
         C2<T>* dst = reinterpret_cast<C2<T>*>(a.p);
-        const unsigned o = (unsigned)(z * a.ny + q) * M + n0, dl = (unsigned)Q * M;
+        const int line = z * a.ny + q;
+        const unsigned o = (unsigned)line * M + n0, dl = (unsigned)Q * M;
+        if (a.need) {
+            const unsigned seg = (unsigned)(2 * n0) >> a.seg_lg;
 #pragma unroll
-        for (int r = 0; r < R; ++r) stg(dst + r * dl, o, v0[0][r]);
+            for (int r = 0; r < R; ++r)
+                if (need_word(a.need, line + Q * r) >> seg & 1u) stg(dst + r * dl, o, v0[0][r]);
+        } else {
+#pragma unroll
+            for (int r = 0; r < R; ++r) stg(dst + r * dl, o, v0[0][r]);
+        }
     }
 }
 
