@@ -883,10 +883,13 @@ int project(dnslab_ctx* x, const T* const us[3], T* const out[3]) {
 // with 8-plane chunks 64^3 (64 blocks) ran 1.11 Gcell-steps/s with single
 // stages against 1.01 with pairs, 128x64x64 (128 blocks) 1.95 against 1.83,
 // 192x96x64 (288) 3.00 either way, the 256x128x96 room (768) 3.80 against
-// 3.95.
+// 3.95.  Below four planes the pairs' four extra ones are the greater part:
+// 2D 1536x192 (nz = 1) 203 -> 170 us per step, 3072x384 450 -> 357, with single
+// stages (512x256x4 301 us with pairs, 314 without).
 bool mom_pairs(const dnslab_ctx* x) {
     if (x->pairs_mode == 0 || !DNSLAB_PAIRS || !mom_pair_supported(x->g, x->Lo.LP)) return false;
-    return x->pairs_mode == 1 || (x->Lo.esz == 8 && x->Lo.LP.nblocks >= DNSLAB_PAIR_MIN_BLOCKS64) ||
+    return x->pairs_mode == 1 ||
+           (x->Lo.esz == 8 && x->g.nz >= 4 && x->Lo.LP.nblocks >= DNSLAB_PAIR_MIN_BLOCKS64) ||
            x->Lo.LP.kc >= DNSLAB_PAIR_MIN_KC;
 }
 // The scalar's second pair reads c^n at the cells around its tile, so it
