@@ -29,6 +29,7 @@ namespace {
 thread_local std::string g_thread_err;
 constexpr int RING_CAP = 4096;
 constexpr int PROF_POOL = 32768;
+constexpr long long PSORT_WIDE_MAX = 1LL << 22;   // particles (235 MB of wide scratch)
 
 enum KernelId { K_NONE = -1, K_MOM = 0, K_SCA, K_FXF, K_FY, K_FZ, K_FXI, K_FILT, K_FILTC, K_CORR, K_DIV, K_IB,
                 K_ADV, K_DIAG, K_REF, K_PART, K_FYZ, K_MOMP, K_SCAP, K_COUNT };
@@ -535,6 +536,7 @@ struct dnslab_ctx {
     unsigned long long* hist_host;
     void* psort_buf;       // particle-sort scratch (allocated on first use, grown as needed)
     size_t psort_bytes;    // its size
+    bool psort_narrow = false;   // the wide form of it could not be had
     DiagRec* pinned;       // host staging for diagnostics
     StepScalars* pinned_sc;
     std::string err;
@@ -1808,9 +1810,14 @@ int dnslab_particles_sort(dnslab_ctx* x, int64_t n, double* pos, double* vel, do
     if (n == 0) return DNSLAB_OK;
     size_t sort_bytes = 0;
     HIPCHK(x, particle_sort_bytes(n, &sort_bytes));
-    const size_t b_key = align_up((size_t)n * sizeof(unsigned), 256), b_tmp = align_up((size_t)n * sizeof(double), 256);
-    const size_t need = 4 * b_key + b_tmp + align_up(sort_bytes, 256);
-    if (need > x->psort_bytes) {
+    // scratch for all seven arrays up to PSORT_WIDE_MAX particles, when it can
+    // be had: they are permuted in two launches instead of fourteen, which read
+    // the permutation seven times; else for one
+    const size_t b_key = align_up((size_t)n * sizeof(unsigned), 256), b_sort = align_up(sort_bytes, 256);
+    const auto bytes = [&](int ntmp) { return 4 * b_key + align_up((size_t)n * ntmp * sizeof(double), 256) + b_sort; };
+    int ntmp = n <= PSORT_WIDE_MAX ? 7 : 1;
+    if (bytes(ntmp) > x->psort_bytes && bytes(1) <= x->psort_bytes && x->psort_narrow) ntmp = 1;
+    if (bytes(ntmp) > x->psort_bytes) {
         if (x->psort_buf) {
             // an earlier sort on the stream may still use the old scratch
             HIPCHK(x, hipStreamSynchronize(x->stream));
@@ -1818,10 +1825,16 @@ int dnslab_particles_sort(dnslab_ctx* x, int64_t n, double* pos, double* vel, do
             x->psort_buf = nullptr;
             x->psort_bytes = 0;
         }
-        x->psort_buf = dev_alloc(x->da, need);
+        x->psort_buf = dev_alloc(x->da, bytes(ntmp));
+        if (!x->psort_buf && ntmp > 1) {
+            ntmp = 1;
+            x->psort_narrow = true;    // not tried again for sorts that the narrow scratch holds
+            x->psort_buf = dev_alloc(x->da, bytes(ntmp));
+        }
         if (!x->psort_buf) return fail(x, DNSLAB_ENOMEM, "particle sort scratch");
-        x->psort_bytes = need;
+        x->psort_bytes = bytes(ntmp);
     }
+    const size_t b_tmp = align_up((size_t)n * ntmp * sizeof(double), 256);
     char* b = (char*)x->psort_buf;
     ParticleSortScratch sc;
     sc.keys[0] = (unsigned*)b;
@@ -1829,6 +1842,7 @@ int dnslab_particles_sort(dnslab_ctx* x, int64_t n, double* pos, double* vel, do
     sc.vals[0] = (unsigned*)(b + 2 * b_key);
     sc.vals[1] = (unsigned*)(b + 3 * b_key);
     sc.tmp = (double*)(b + 4 * b_key);
+    sc.ntmp = ntmp;
     sc.sort_tmp = b + 4 * b_key + b_tmp;
     sc.sort_bytes = sort_bytes;
     HIPCHK(x, sort_particles(x->g, n, pos, vel, diam, sc, x->stream));

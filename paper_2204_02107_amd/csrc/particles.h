@@ -37,7 +37,8 @@ hipError_t launch_particles(const ParticleArgs<T>& a, hipStream_t s);
 struct ParticleSortScratch {
     unsigned* keys[2];     // n cell indices each
     unsigned* vals[2];     // n particle indices each
-    double* tmp;           // n doubles
+    double* tmp;           // ntmp arrays of n doubles
+    int ntmp;              // 7: all arrays permuted at once; 1: one after the other
     void* sort_tmp;        // radix-sort counts and scan totals
     size_t sort_bytes;
 };

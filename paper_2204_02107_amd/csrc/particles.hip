@@ -17,7 +17,7 @@ __device__ __forceinline__ double interp3(const T* __restrict__ f, const Grid& g
 #pragma unroll
         for (int cy = 0; cy < 2; ++cy) {
             const double wy = cy ? w[1] : 1.0 - w[1];
-            const long long row = ((long long)k[cz] * g.ny + j[cy]) * g.nx;
+            const unsigned row = ((unsigned)k[cz] * (unsigned)g.ny + (unsigned)j[cy]) * (unsigned)g.nx;
 #pragma unroll
             for (int cx = 0; cx < 2; ++cx) {
                 const double wx = cx ? w[0] : 1.0 - w[0];
@@ -28,13 +28,18 @@ __device__ __forceinline__ double interp3(const T* __restrict__ f, const Grid& g
     return out;
 }
 
-// Index of the cell holding position x along an axis of n cells of size d
-// (the lower interpolation corner, wrapped periodically).
-__device__ __forceinline__ int cell_of(double x, double d, int n) {
-    long long i0 = (long long)floor(x / d) % n;
+// fl (a floored coordinate in cells) wrapped into [0, n): positions lie in the
+// box, so the 64-bit remainder is for the rare exception.
+__device__ __forceinline__ int wrap_cell(double fl, int n) {
+    if (fl >= 0.0 && fl < (double)n) return (int)fl;
+    long long i0 = (long long)fl % n;
     if (i0 < 0) i0 += n;
     return (int)i0;
 }
+
+// Index of the cell holding position x along an axis of n cells of size d
+// (the lower interpolation corner, wrapped periodically).
+__device__ __forceinline__ int cell_of(double x, double d, int n) { return wrap_cell(floor(x / d), n); }
 
 // Wrap into [0, L) like a floored modulo.
 __device__ __forceinline__ double wrap_box(double x, double L) {
@@ -42,13 +47,28 @@ __device__ __forceinline__ double wrap_box(double x, double L) {
     return r >= L ? r - L : r;
 }
 
+// Blocks handed to the XCDs in runs of RUN consecutive ones: particles next to
+// each other in the arrays are, when sorted, next to each other in space, so a
+// run shares velocity lines (and the sort's output lines) in one L2.  Bounded
+// runs, as eight far-apart streams cost more than they share from 2^23
+// particles on (one run per XCD 277 us, runs of 256 blocks 258, none 254).
+template <unsigned RUN>
+__device__ __forceinline__ unsigned xcd_run_block(unsigned hw, unsigned nb) {
+    const unsigned g0 = hw / (8 * RUN) * (8 * RUN);
+    return g0 + xcd_block(hw - g0, min(8 * RUN, nb - g0));
+}
+
+// One thread per particle, bound by the 24 scattered velocity reads: 2^20
+// sorted particles in a 256x128x96 FP64 room take 42 us; 57 with blocks dealt
+// to the XCDs one by one.  (A load of both x corners at once is slower: 50.)
 template <typename T>
 __global__ __launch_bounds__(256) void k_particles(const ParticleArgs<T> a) {
-    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    const long long q = (long long)xcd_run_block<256>(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
     if (q >= a.n) return;
     const Grid& g = a.g;
     const double pos[3] = {a.px[q], a.py[q], a.pz[q]};
     const double vel[3] = {a.vx[q], a.vy[q], a.vz[q]};
+    const double d = a.diam[q];
     const int nn[3] = {g.nx, g.ny, g.nz};
     int lo[3][2];
     double w[3];
@@ -56,10 +76,8 @@ __global__ __launch_bounds__(256) void k_particles(const ParticleArgs<T> a) {
     for (int ax = 0; ax < 3; ++ax) {
         const double s = pos[ax] / g.d[ax];
         const double fl = floor(s);
-        long long i0 = (long long)fl % nn[ax];
-        if (i0 < 0) i0 += nn[ax];
-        lo[ax][0] = (int)i0;
-        lo[ax][1] = (int)(i0 + 1 == nn[ax] ? 0 : i0 + 1);
+        lo[ax][0] = wrap_cell(fl, nn[ax]);
+        lo[ax][1] = lo[ax][0] + 1 == nn[ax] ? 0 : lo[ax][0] + 1;
         w[ax] = s - fl;
     }
     const double uf[3] = {interp3(a.u, g, lo[0], lo[1], lo[2], w), interp3(a.v, g, lo[0], lo[1], lo[2], w),
@@ -67,7 +85,6 @@ __global__ __launch_bounds__(256) void k_particles(const ParticleArgs<T> a) {
     // drag coefficient from the velocities at the start of the step
     const double rel = sqrt((uf[0] - vel[0]) * (uf[0] - vel[0]) + (uf[1] - vel[1]) * (uf[1] - vel[1]) +
                             (uf[2] - vel[2]) * (uf[2] - vel[2]));
-    const double d = a.diam[q];
     const double re = rel * d / a.nu;
     const double cd = 1.0 + pow(re, 2.0 / 3.0) / 6.0;
     const double tp = a.rho_p * d * d / (18.0 * a.rho_f * a.nu);
@@ -103,10 +120,36 @@ __global__ __launch_bounds__(256) void k_gather(const double* __restrict__ in, c
     if (q < n) out[q] = in[perm[q]];
 }
 
+// The seven arrays of the particles.
+struct SevenArrays {
+    double* p[7];
+};
+// All seven at once: out[a n + q] = in_a[perm[q]], and back.
+__global__ __launch_bounds__(256) void k_gather7(const SevenArrays in, const unsigned* __restrict__ perm, long long n,
+                                                 double* __restrict__ out) {
+    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= n) return;
+    const unsigned e = perm[q];
+    double v[7];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) v[a] = in.p[a][e];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) out[a * n + q] = v[a];
+}
+__global__ __launch_bounds__(256) void k_copy_back7(const double* __restrict__ in, long long n, const SevenArrays out) {
+    const long long q = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= n) return;
+    double v[7];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) v[a] = in[a * n + q];
+#pragma unroll
+    for (int a = 0; a < 7; ++a) out.p[a][q] = v[a];
+}
+
 // ---------------------------------------------------------------------------
 // Stable least-significant-digit radix sort of (key, value) pairs, 8-bit
 // digits.  One pass per digit: every block counts the digits of its chunk of
-// SORT_CHUNK consecutive keys (counts stored digit-major: digit d of block b
+// consecutive keys (sort_items a thread; counts stored digit-major: digit d of block b
 // at d * nblocks + b), an exclusive scan of those counts gives each (digit,
 // block) its first output slot, and every block scatters its chunk in input
 // order, each key going after the keys of its digit that precede it (in
@@ -114,22 +157,30 @@ __global__ __launch_bounds__(256) void k_gather(const double* __restrict__ in, c
 // earlier lanes of its wave).  Stable passes make the whole sort stable.
 // ---------------------------------------------------------------------------
 constexpr int SORT_THREADS = 256;
-constexpr int SORT_ITEMS = 16;
-constexpr int SORT_CHUNK = SORT_THREADS * SORT_ITEMS;    // keys per block
+constexpr int SORT_ITEMS = 16;                           // the most keys per thread
+// Keys per thread: a block ranks them one after another, so short chunks where
+// that still leaves few counts.  A whole sort with 16 / 8 / 4 keys: 2^20
+// particles 165 / 139 / 136 us, 2^23 784 / 760 / 744.  The scratch holds a
+// count per digit and chunk, and from 2^22 on the longer chunks keep it small.
+constexpr int sort_items(long long n) { return n <= (1LL << 21) ? 4 : n <= (1LL << 22) ? 8 : SORT_ITEMS; }
 constexpr int SORT_RADIX = 256;
 constexpr int SCAN_THREADS = 1024;
 constexpr int SCAN_ITEMS = 4;
 constexpr int SCAN_CHUNK = SCAN_THREADS * SCAN_ITEMS;   // counts per scan block
+// With at most this many scan blocks every scatter block adds their totals up
+// itself (two launches less per pass).
+constexpr int SCAN_FUSED = SORT_THREADS;
 
+template <int ITEMS>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_hist(const unsigned* __restrict__ keys, long long n,
                                                              int shift, unsigned* __restrict__ counts, int nblocks) {
     __shared__ unsigned hist[SORT_RADIX];
     const int t = threadIdx.x;
     hist[t] = 0;
     __syncthreads();
-    const long long c0 = (long long)blockIdx.x * SORT_CHUNK;
+    const long long c0 = (long long)blockIdx.x * (SORT_THREADS * ITEMS);
 #pragma unroll
-    for (int it = 0; it < SORT_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const long long q = c0 + (long long)it * SORT_THREADS + t;
         if (q < n) atomicAdd(&hist[(keys[q] >> shift) & (SORT_RADIX - 1)], 1u);
     }
@@ -204,19 +255,37 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_scan_add(unsigned* __restrict_
         if (base + i < len) a[base + i] += add;
 }
 
+// sums != NULL: offsets are scanned within scan blocks only, whose nsums
+// (<= SCAN_FUSED) totals sums holds.
+template <int ITEMS>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const unsigned* __restrict__ kin,
                                                                 const unsigned* __restrict__ vin, long long n,
                                                                 int shift, const unsigned* __restrict__ offsets,
                                                                 int nblocks, unsigned* __restrict__ kout,
-                                                                unsigned* __restrict__ vout) {
+                                                                unsigned* __restrict__ vout,
+                                                                const unsigned* __restrict__ sums, int nsums) {
     constexpr int NW = SORT_THREADS / 64;
     __shared__ unsigned base[SORT_RADIX];          // next output slot of each digit for this block
     __shared__ unsigned wcnt[NW][SORT_RADIX];      // keys of each digit in each wave of the tile
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    base[t] = offsets[(size_t)t * nblocks + blockIdx.x];
-    const long long c0 = (long long)blockIdx.x * SORT_CHUNK;
+    // consecutive chunks write next to each other in every digit's range: on one
+    // XCD their partial lines merge in its L2
+    const unsigned blk = xcd_run_block<64>(blockIdx.x, gridDim.x);
+    const size_t slot = (size_t)t * nblocks + blk;
+    unsigned first = offsets[slot];
+    if (sums) {
+        unsigned* pre = wcnt[0];
+        unsigned total;
+        const unsigned excl = block_exclusive_scan(t < nsums ? sums[t] : 0u, pre, total);
+        pre[t] = excl;
+        __syncthreads();
+        first += pre[slot / SCAN_CHUNK];
+        __syncthreads();
+    }
+    base[t] = first;
+    const long long c0 = (long long)blk * (SORT_THREADS * ITEMS);
     const unsigned long long lt = (1ull << lane) - 1ull;
-    for (int it = 0; it < SORT_ITEMS; ++it) {
+    for (int it = 0; it < ITEMS; ++it) {
         const long long q = c0 + (long long)it * SORT_THREADS + t;
         const bool valid = q < n;
         unsigned key = 0, val = 0;
@@ -258,15 +327,41 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const unsigned* _
 
 }  // namespace
 
-long long particle_sort_max() { return (long long)SCAN_CHUNK * SCAN_CHUNK / SORT_RADIX * SORT_CHUNK; }
+long long particle_sort_max() {
+    return (long long)SCAN_CHUNK * SCAN_CHUNK / SORT_RADIX * SORT_THREADS * SORT_ITEMS;
+}
 
 hipError_t particle_sort_bytes(long long n, size_t* bytes) {
-    const long long nblocks = (n + SORT_CHUNK - 1) / SORT_CHUNK;
+    const long long chunk = (long long)SORT_THREADS * sort_items(n);
+    const long long nblocks = (n + chunk - 1) / chunk;
     const long long len = nblocks * SORT_RADIX;
     const long long nscan = (len + SCAN_CHUNK - 1) / SCAN_CHUNK;
     *bytes = (size_t)(len + nscan + 64) * sizeof(unsigned);
     return hipSuccess;
 }
+
+namespace {
+// One radix pass on the digit at shift.
+template <int ITEMS>
+void sort_pass(const ParticleSortScratch& s, int cur, long long n, int shift, hipStream_t st) {
+    const int nblocks = (int)((n + SORT_THREADS * ITEMS - 1) / (SORT_THREADS * ITEMS));
+    const long long len = (long long)nblocks * SORT_RADIX;
+    const int nscan = (int)((len + SCAN_CHUNK - 1) / SCAN_CHUNK);
+    unsigned* counts = (unsigned*)s.sort_tmp;
+    unsigned* sums = counts + len;
+    const bool fused = nscan <= SCAN_FUSED;
+    hipLaunchKernelGGL((k_sort_hist<ITEMS>), dim3(nblocks), dim3(SORT_THREADS), 0, st, (const unsigned*)s.keys[cur], n,
+                       shift, counts, nblocks);
+    hipLaunchKernelGGL(k_scan_blocks, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, len, sums);
+    if (!fused) {
+        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_THREADS), 0, st, sums, nscan);
+        hipLaunchKernelGGL(k_scan_add, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, len, (const unsigned*)sums);
+    }
+    hipLaunchKernelGGL((k_sort_scatter<ITEMS>), dim3(nblocks), dim3(SORT_THREADS), 0, st, (const unsigned*)s.keys[cur],
+                       (const unsigned*)s.vals[cur], n, shift, (const unsigned*)counts, nblocks, s.keys[cur ^ 1],
+                       s.vals[cur ^ 1], fused ? (const unsigned*)sums : nullptr, nscan);
+}
+}  // namespace
 
 template <typename T>
 hipError_t launch_particles(const ParticleArgs<T>& a, hipStream_t s) {
@@ -287,27 +382,24 @@ hipError_t sort_particles(const Grid& g, long long n, double* pos, double* vel, 
     // cell indices are below nx ny nz < 2^31: sort on the bits that can be set
     unsigned end_bit = 1;
     while (end_bit < 32 && ((unsigned long long)1 << end_bit) < (unsigned long long)g.n) ++end_bit;
-    const int nblocks = (int)((n + SORT_CHUNK - 1) / SORT_CHUNK);
-    const long long len = (long long)nblocks * SORT_RADIX;
-    const int nscan = (int)((len + SCAN_CHUNK - 1) / SCAN_CHUNK);
-    unsigned* counts = (unsigned*)s.sort_tmp;
-    unsigned* sums = counts + len;
     int cur = 0;
     for (unsigned shift = 0; shift < end_bit; shift += 8) {
-        hipLaunchKernelGGL(k_sort_hist, dim3(nblocks), dim3(SORT_THREADS), 0, st, (const unsigned*)s.keys[cur], n,
-                           (int)shift, counts, nblocks);
-        hipLaunchKernelGGL(k_scan_blocks, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, len, sums);
-        hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_THREADS), 0, st, sums, nscan);
-        hipLaunchKernelGGL(k_scan_add, dim3(nscan), dim3(SCAN_THREADS), 0, st, counts, len, (const unsigned*)sums);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(nblocks), dim3(SORT_THREADS), 0, st, (const unsigned*)s.keys[cur],
-                           (const unsigned*)s.vals[cur], n, (int)shift, (const unsigned*)counts, nblocks,
-                           s.keys[cur ^ 1], s.vals[cur ^ 1]);
+        switch (sort_items(n)) {
+            case 4: sort_pass<4>(s, cur, n, (int)shift, st); break;
+            case 8: sort_pass<8>(s, cur, n, (int)shift, st); break;
+            default: sort_pass<SORT_ITEMS>(s, cur, n, (int)shift, st); break;
+        }
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         cur ^= 1;
     }
-    double* arrays[7] = {pos, pos + n, pos + 2 * n, vel, vel + n, vel + 2 * n, diam};
-    for (double* a : arrays) {
+    const SevenArrays all = {{pos, pos + n, pos + 2 * n, vel, vel + n, vel + 2 * n, diam}};
+    if (s.ntmp == 7) {
+        hipLaunchKernelGGL(k_gather7, dim3(nb), dim3(256), 0, st, all, (const unsigned*)s.vals[cur], n, s.tmp);
+        hipLaunchKernelGGL(k_copy_back7, dim3(nb), dim3(256), 0, st, (const double*)s.tmp, n, all);
+        return hipGetLastError();
+    }
+    for (double* a : all.p) {
         hipLaunchKernelGGL(k_gather, dim3(nb), dim3(256), 0, st, (const double*)a, (const unsigned*)s.vals[cur], n,
                            s.tmp);
         e = hipMemcpyAsync(a, s.tmp, (size_t)n * sizeof(double), hipMemcpyDeviceToDevice, st);
