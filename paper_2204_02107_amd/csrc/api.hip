@@ -116,7 +116,7 @@ struct Layout {
     int nparts;            // partial-result slots (max block count of the reducing kernels)
     int nfields;           // work fields: 13, plus 3 for the projected velocity when the filter is on
     // byte offsets inside the workspace
-    size_t off_flags, off_fields, off_spec, off_need, off_tw, off_s2, off_forced, off_part, off_sc, off_ring;
+    size_t off_flags, off_fields, off_spec, off_need, off_tw, off_s2, off_forced, off_fseg, off_part, off_sc, off_ring;
     size_t total;
     int nforced_cap;
 };
@@ -475,7 +475,8 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     Lo.off_tw = take((size_t)(Lo.m + P->ny + P->nz + Lo.m + 1) * csz);
     Lo.off_s2 = take((size_t)(Lo.m + 1 + P->ny + P->nz) * sizeof(double));
     Lo.nforced_cap = std::max(1, n_forced);
-    Lo.off_forced = take((size_t)Lo.nforced_cap * (sizeof(long long) + 5 * sizeof(double)));
+    Lo.off_forced = take((size_t)Lo.nforced_cap * 5 * sizeof(double));
+    Lo.off_fseg = take(n_forced > 0 ? ((size_t)g.n + 63) / 64 * sizeof(ForcedSeg) : 0);
     Lo.off_part = take((size_t)PF_COUNT * Lo.nparts * sizeof(double));
     Lo.off_sc = take(sizeof(StepScalars));
     Lo.off_ring = take((size_t)RING_CAP * sizeof(DiagRec));
@@ -519,7 +520,7 @@ struct dnslab_ctx {
     void* spec;
     void *wx, *wy, *wz, *tw;
     double *sx2, *sy2, *sz2;
-    long long* fidx;
+    ForcedSeg* fseg;
     double *fS, *fuset, *fcset;
     int nforced;
     PartSoA part;
@@ -625,7 +626,7 @@ struct Prof {
 template <typename T>
 Forcing forcing_of(dnslab_ctx* x) {
     Forcing f;
-    f.idx = x->fidx;
+    f.seg = x->fseg;
     f.S = x->fS;
     f.uset = x->fuset;
     f.cset = x->fcset;
@@ -1545,8 +1546,8 @@ int dnslab_init(const dnslab_params* params, const uint8_t* beta_dev, int64_t n_
         x->sx2 = (double*)(base + Lo.off_s2);
         x->sy2 = x->sx2 + Lo.m + 1;
         x->sz2 = x->sy2 + params->ny;
-        x->fidx = (long long*)(base + Lo.off_forced);
-        x->fS = (double*)(x->fidx + Lo.nforced_cap);
+        x->fseg = (ForcedSeg*)(base + Lo.off_fseg);
+        x->fS = (double*)(base + Lo.off_forced);
         x->fuset = x->fS + Lo.nforced_cap;
         x->fcset = x->fuset + 3 * (size_t)Lo.nforced_cap;
         x->part = PartSoA{(double*)(base + Lo.off_part), Lo.nparts};
@@ -1568,11 +1569,11 @@ int dnslab_init(const dnslab_params* params, const uint8_t* beta_dev, int64_t n_
         rc = build_flags(x, beta_dev, fidx_h.data(), n_forced, room_mask_dev);
         if (rc == DNSLAB_OK && n_forced > 0) {
             const hipStream_t st = x->stream;
-            if (hipMemcpyAsync(x->fidx, forced_idx_dev, n_forced * sizeof(long long), hipMemcpyDeviceToDevice, st) != hipSuccess ||
+            if (launch_forced_segs((const long long*)forced_idx_dev, (int)n_forced, x->fseg, st) != hipSuccess ||
                 hipMemcpyAsync(x->fS, forced_S_dev, n_forced * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess ||
                 hipMemcpyAsync(x->fuset, forced_uset_dev, 3 * n_forced * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess ||
                 hipMemcpyAsync(x->fcset, forced_cset_dev, n_forced * sizeof(double), hipMemcpyDeviceToDevice, st) != hipSuccess)
-                rc = fail(x, DNSLAB_EHIP, "copying forcing arrays failed");
+                rc = fail(x, DNSLAB_EHIP, "laying out the forcing arrays failed");
         }
         if (rc == DNSLAB_OK) rc = Lo.esz == 8 ? upload_tables<double>(x) : upload_tables<float>(x);
         if (rc == DNSLAB_OK) {

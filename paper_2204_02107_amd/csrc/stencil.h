@@ -165,6 +165,9 @@ struct StencilLaunch {
 // cells_x: cells per thread along x (1, or 2 for the pair kernels).
 StencilLaunch stencil_launch(const Grid& g, int rows, int kc, int cells_x);
 
+// The segment table of the n sorted cell indices idx (device memory).
+hipError_t launch_forced_segs(const long long* idx, int n, ForcedSeg* seg, hipStream_t s);
+
 // Every launch_* issues one kernel on stream s, or, when rec is non-NULL,
 // records the launch (for batched replay by the pool) without issuing it.
 template <typename T> hipError_t launch_mom_stage(int mode, const MomArgs<T>& a, const StencilLaunch& L, hipStream_t s,

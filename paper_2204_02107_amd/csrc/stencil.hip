@@ -206,7 +206,7 @@ __device__ __forceinline__ void mom_rhs_cell(const MomCoef<T>& cf, const T z0[3]
         kv[c] = -C + cf.nu * L + cf.b[c];
     }
     if (fl & F_FORCED) {
-        const int e = forced_entry(frc, (long long)idx);
+        const int e = forced_entry(frc, idx);
         const T S = T(frc.S[e]) * T(frc.inv_tau);
 #pragma unroll
         for (int c = 0; c < 3; ++c) kv[c] += S * (T(frc.uset[3 * e + c]) - z0[c]);
@@ -814,19 +814,18 @@ __device__ __forceinline__ T sca_rhs_cell(const ScaCoef<T>& cf, T c0, T cxm, T c
                                           T uxm, T uxp, T vym, T vyp, T wm, T wp, uint8_t f0, uint8_t fxm,
                                           uint8_t fxp, uint8_t fym, uint8_t fyp, uint8_t fm, uint8_t fp,
                                           const Forcing& frc, unsigned idx) {
-    T G = T(0);
-    if (f0 & F_FLUID) {
-        const T conv = (uxp * cxp - uxm * cxm) * cf.h2x + (vyp * cyp - vym * cym) * cf.h2y + (wp * cp - wm * cm) * cf.h2z;
-        const T lx = ((fxp & F_FLUID) ? cxp - c0 : T(0)) - ((fxm & F_FLUID) ? c0 - cxm : T(0));
-        const T ly = ((fyp & F_FLUID) ? cyp - c0 : T(0)) - ((fym & F_FLUID) ? c0 - cym : T(0));
-        const T lz = ((fp & F_FLUID) ? cp - c0 : T(0)) - ((fm & F_FLUID) ? c0 - cm : T(0));
-        G = -conv + cf.alpha * (lx * cf.ix2 + ly * cf.iy2 + lz * cf.iz2);
-        if (f0 & F_FORCED) {
-            const int e = forced_entry(frc, (long long)idx);
-            G += T(frc.S[e]) * T(frc.inv_tau) * (T(frc.cset[e]) - c0);
-        }
+    const T conv = (uxp * cxp - uxm * cxm) * cf.h2x + (vyp * cyp - vym * cym) * cf.h2y + (wp * cp - wm * cm) * cf.h2z;
+    const T lx = ((fxp & F_FLUID) ? cxp - c0 : T(0)) - ((fxm & F_FLUID) ? c0 - cxm : T(0));
+    const T ly = ((fyp & F_FLUID) ? cyp - c0 : T(0)) - ((fym & F_FLUID) ? c0 - cym : T(0));
+    const T lz = ((fp & F_FLUID) ? cp - c0 : T(0)) - ((fm & F_FLUID) ? c0 - cm : T(0));
+    T G = -conv + cf.alpha * (lx * cf.ix2 + ly * cf.iy2 + lz * cf.iz2);
+    if (f0 & F_FORCED) {
+        const int e = forced_entry(frc, idx);
+        G += T(frc.S[e]) * T(frc.inv_tau) * (T(frc.cset[e]) - c0);
     }
-    return G;
+    // no branch on the flags: the compiler would move the loads above into it,
+    // where they wait for the flags
+    return (f0 & F_FLUID) ? G : T(0);
 }
 
 template <typename T, int MODE>
@@ -1961,6 +1960,17 @@ __device__ __forceinline__ DiagArgs from_table(const DiagArgs& t) {
     return a;
 }
 
+// The first entry of each segment writes the segment's record.
+__global__ __launch_bounds__(256) void k_forced_segs(const long long* __restrict__ idx, int n, ForcedSeg* __restrict__ seg) {
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= n) return;
+    const long long sg = idx[e] >> 6;
+    if (e > 0 && idx[e - 1] >> 6 == sg) return;
+    unsigned long long mask = 0;
+    for (int q = e; q < n && idx[q] >> 6 == sg; ++q) mask |= 1ull << (idx[q] & 63);
+    seg[sg] = ForcedSeg{mask, (unsigned long long)e};
+}
+
 template <typename T, int MODE, bool LDS>
 __global__ __launch_bounds__(1024) void k_mom_stage(const MomArgs<T> a) { mom_stage_body<T, MODE, LDS>(a, hw_block()); }
 template <typename T, int MODE, bool LDS>
@@ -2443,6 +2453,12 @@ hipError_t launch_batched_stencil(int kind, const void* tab, const unsigned* st,
     }
     return fp32 ? batched_typed<float>(base, mode, tab, st, ns, nb, blk, lds, s)
                 : batched_typed<double>(base, mode, tab, st, ns, nb, blk, lds, s);
+}
+
+hipError_t launch_forced_segs(const long long* idx, int n, ForcedSeg* seg, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_forced_segs, dim3((n + 255) / 256), dim3(256), 0, s, idx, n, seg);
+    return hipGetLastError();
 }
 
 hipError_t launch_set_rate(PartSoA part, int np, StepScalars* sc, hipStream_t s) {
