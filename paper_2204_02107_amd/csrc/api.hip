@@ -268,47 +268,24 @@ Grid make_grid(const dnslab_params* P) {
 #ifndef DNSLAB_PAIRS
 #define DNSLAB_PAIRS 1         // RK4 stages two at a time (fused stage pairs) where the tile divides the grid
 #endif
-#ifndef DNSLAB_PAIR_MIN_BLOCKS64
-#define DNSLAB_PAIR_MIN_BLOCKS64 256   // FP64 momentum pairs from this many blocks on (mom_pairs)
+#ifndef DNSLAB_PAIR_MIN_CELLS64
+#define DNSLAB_PAIR_MIN_CELLS64 (1LL << 20)   // stage pairs from this grid size on (mom_pairs)
 #endif
-#ifndef DNSLAB_PAIR_MIN_KC
-#define DNSLAB_PAIR_MIN_KC 16  // shortest z chunk for the scalar pairs and the FP32 momentum pairs
+#ifndef DNSLAB_PAIR_MIN_CELLS32
+#define DNSLAB_PAIR_MIN_CELLS32 (1LL << 21)
 #endif
-#ifndef DNSLAB_PKC_DIV
-#define DNSLAB_PKC_DIV 1024    // stage-pair z chunk: nz * tiles per plane / this, clamped to [8, DNSLAB_PKC_MAX]
-#endif
-#ifndef DNSLAB_PKC_MAX
-#define DNSLAB_PKC_MAX 32
-#endif
-// Longer stage-pair chunks where they still give this many blocks (the pair
-// kernels re-read 4 halo planes and recompute 2 planes of the first stage per
-// chunk).
-#ifndef DNSLAB_PKC_LONG
-#define DNSLAB_PKC_LONG 128
-#endif
-#ifndef DNSLAB_PKC_LONG_BLOCKS
-#define DNSLAB_PKC_LONG_BLOCKS 2048
-#endif
-#ifndef DNSLAB_PKC_LONG32
-#define DNSLAB_PKC_LONG32 64
-#endif
-#ifndef DNSLAB_PKC_LONG_BLOCKS32
-#define DNSLAB_PKC_LONG_BLOCKS32 4096
+#ifndef DNSLAB_PAIR_MIN_NZ
+#define DNSLAB_PAIR_MIN_NZ 4
 #endif
 
-// Grids below DNSLAB_SMALL_CELLS leave most CUs idle with the usual chunks and
-// are bound by the length of a block's march: radius-1 stencils then take one
-// plane per block, the filter 64 x 4 tiles and 4 planes (DNSLAB_FILTER_SMALL_CELLS).
-// Measured per step, FP64 / FP32: 64^3 188 -> 157 / 200 -> 169 us, 128x64x64
-// 222 -> 189 / 214 -> 194; 192x96x64 FP32 284 -> 274 (filter 28 -> 20 us, its
-// radius-1 stencils one plane faster in FP32 alone, 2 planes there); one plane
-// on 256x128x96 was slower (650 -> 662, 470 -> 483), two in FP32 faster
-// (460).
+// Grids up to DNSLAB_SMALL_CELLS leave CUs idle with the usual chunks and are
+// bound by the length of a block's march: radius-1 stencils then take two
+// planes per block, the filter 64 x 4 tiles and 4 planes (DNSLAB_FILTER_SMALL_CELLS).
+// Step with chunks of 1 / 2 / 4 planes: 64^3 FP64 157 / 157 / 163 us, FP32 163 /
+// 166 / 181; 128x64x64 FP64 191 / 185 / 191; 192x96x64 FP32 266 / 255 / 256;
+// 108x72x54 FP64 205 / 204 / 213.
 #ifndef DNSLAB_SMALL_CELLS
-#define DNSLAB_SMALL_CELLS (1LL << 19)
-#endif
-#ifndef DNSLAB_SMALL_CELLS32
-#define DNSLAB_SMALL_CELLS32 (1LL << 22)   // FP32: two planes up to this
+#define DNSLAB_SMALL_CELLS (1LL << 21)
 #endif
 #ifndef DNSLAB_FILTER_SMALL_CELLS
 #define DNSLAB_FILTER_SMALL_CELLS (1LL << 21)
@@ -326,6 +303,28 @@ int stencil_kc(const Grid& g, int rows, int forced, int kc_min = 4) {
     long long kc = (long long)g.nz * cols / 4096;
     kc = std::max<long long>(kc_min, std::min(32LL, kc));
     return (int)std::min<long long>(kc, g.nz);
+}
+
+// z chunk of a kernel whose block reads halo planes beside those it completes
+// and keeps a CU busy by itself (64 x rows tiles, `slots` blocks at a time on
+// the chip): the launch takes as long as the CU with the most blocks, so the
+// chunk that makes (rounds of slots blocks) (kc + halo) least.  Beyond one round
+// the blocks of neighbouring tiles drift apart and fetch their common rows
+// twice, so chunks end at `cap` planes there.
+int march_chunk(const Grid& g, int rows, int halo, int slots, int cap) {
+    const StencilLaunch one = stencil_launch(g, rows, g.nz, 1);
+    const long long cols = (long long)one.grid.x * one.grid.y;
+    long long best = 0;
+    int kc_best = std::min(g.nz, 4);
+    for (int nch = 1; nch <= g.nz; ++nch) {
+        const int kc = (g.nz + nch - 1) / nch;
+        if (kc < 4 && nch > 1) break;
+        const long long nb = cols * ((g.nz + kc - 1) / kc), rounds = (nb + slots - 1) / slots;
+        if (rounds > 1 && kc > cap) continue;
+        const long long t = rounds * (kc + halo);
+        if (best == 0 || t < best) { best = t; kc_best = kc; }
+    }
+    return kc_best;
 }
 
 Layout make_layout(const dnslab_params* P, int n_forced) {
@@ -420,7 +419,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
             }
         }
     }
-    const int kc_min = g.n <= DNSLAB_SMALL_CELLS ? 1 : Lo.esz == 4 && g.n <= DNSLAB_SMALL_CELLS32 ? 2 : 4;
+    const int kc_min = g.n <= DNSLAB_SMALL_CELLS ? 2 : 4;
     Lo.L = stencil_launch(g, DNSLAB_ROWS, stencil_kc(g, DNSLAB_ROWS, DNSLAB_KC, kc_min), 1);
     Lo.L1 = Lo.L;
     // Filter and correction: 64 x DNSLAB_FROWS tiles with long z chunks (the
@@ -446,18 +445,16 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
             Lo.LF = stencil_launch(g, 8, std::max(stencil_kc(g, 8, DNSLAB_FKC), std::min(small_min, P->nz)), 1);
     }
     {
-        // the pair kernels read kc + 4 planes and evaluate their first stage on
-        // kc + 2 planes per chunk: longer chunks than the single-stage kernels
-        const StencilLaunch one = stencil_launch(g, DNSLAB_PROWS, g.nz, 1);
-        const long long cols = (long long)one.grid.x * one.grid.y;
-        const long long pkc = std::max(8LL, std::min((long long)DNSLAB_PKC_MAX, (long long)g.nz * cols / DNSLAB_PKC_DIV));
-        Lo.LP = stencil_launch(g, DNSLAB_PROWS, (int)std::min<long long>(pkc, g.nz), 1);
-        const int long_kc = Lo.esz == 8 ? DNSLAB_PKC_LONG : DNSLAB_PKC_LONG32;
-        const int long_blocks = Lo.esz == 8 ? DNSLAB_PKC_LONG_BLOCKS : DNSLAB_PKC_LONG_BLOCKS32;
-        if (Lo.LP.kc < long_kc) {
-            const StencilLaunch lp = stencil_launch(g, DNSLAB_PROWS, std::min(long_kc, g.nz), 1);
-            if (lp.nblocks >= long_blocks) Lo.LP = lp;
-        }
+        // Stage pairs: one FP64 block nearly fills a CU's share of the
+        // bandwidth, FP32 blocks only two at a time.  Two momentum and two scalar
+        // pairs, FP64: 256x128x96 279 us in 24-plane chunks (one block per CU),
+        // 297 in 12 (two), 322 in 8 (three), 310 in 16 (one and a half);
+        // 512x256x192 1665 in 192 (one), 1720 in 96, 1849 in 32; 1024x512x256 9.05
+        // ms in 256 (four), 8.84 in 128, 9.32 in 64.  FP32: 256x128x96 158 in 12,
+        // 180 in 8, 211 in 24; 512x256x192 980 in 96, 1027 in 32; 1024x512x256
+        // step 14.14 ms in 128, 13.97 in 64.
+        Lo.LP = stencil_launch(g, DNSLAB_PROWS,
+                               Lo.esz == 8 ? march_chunk(g, DNSLAB_PROWS, 4, 256, 128) : march_chunk(g, DNSLAB_PROWS, 4, 512, 64), 1);
     }
     Lo.LC = ring_geometry ? Lo.LF : Lo.L1;
     Lo.nparts = std::max(std::max(std::max(Lo.L.nblocks, Lo.L1.nblocks), Lo.LF.nblocks), Lo.LP.nblocks);
@@ -873,35 +870,25 @@ int project(dnslab_ctx* x, const T* const us[3], T* const out[3]) {
     return rc;
 }
 
-// RK4 stages two per pass where the pair kernels' tile divides the grid and
-// the grid gives each block a z chunk long enough for the pipeline's four
-// extra planes: measured, the momentum pairs gain on 256x128x96 in FP64
-// (8-plane chunks: 261 -> 224 us per step) but lose in FP32 (139 -> 152 us),
-// and the scalar pairs lose on it in both (152 -> 189, 104 -> 137 us), while
-// on 1024x512x256 (32-plane chunks) both gain (FP64 momentum 12.0 -> 6.6 ms,
-// scalar 7.6 -> 5.2 ms per step).
+// RK4 stages two per pass where the pair kernels' tile divides the grid, it
+// has enough cells to fill the chip with pair blocks and more planes than the
+// four that a pair reads beside its own.  Momentum + scalar kernels of a step,
+// pairs / single stages: FP64 192x96x64 129 / 160 us, 128x64x64 85 / 92 (the
+// step 192 / 185: the pairs overlap less), 256x128x96 279 / 392; FP32 192x96x64
+// 103 / 100, 256x128x64 119 / 145, 384x144x96 260 / 348.  2D 1536x192 (nz = 1)
+// FP64: step 203 us with pairs, 170 without.
 // dnslab_set_stage_pairs overrides the choice (pairs_mode 0: never, 1:
 // wherever supported).
-// FP64 momentum pairs on short z chunks pay only with a block per CU or more:
-// with 8-plane chunks 64^3 (64 blocks) ran 1.11 Gcell-steps/s with single
-// stages against 1.01 with pairs, 128x64x64 (128 blocks) 1.95 against 1.83,
-// 192x96x64 (288) 3.00 either way, the 256x128x96 room (768) 3.80 against
-// 3.95.  Below four planes the pairs' four extra ones are the greater part:
-// 2D 1536x192 (nz = 1) 203 -> 170 us per step, 3072x384 450 -> 357, with single
-// stages (512x256x4 301 us with pairs, 314 without).
-bool mom_pairs(const dnslab_ctx* x) {
+bool stage_pairs(const dnslab_ctx* x) {
     if (x->pairs_mode == 0 || !DNSLAB_PAIRS || !mom_pair_supported(x->g, x->Lo.LP)) return false;
-    return x->pairs_mode == 1 ||
-           (x->Lo.esz == 8 && x->g.nz >= 4 && x->Lo.LP.nblocks >= DNSLAB_PAIR_MIN_BLOCKS64) ||
-           x->Lo.LP.kc >= DNSLAB_PAIR_MIN_KC;
+    return x->pairs_mode == 1 || (x->g.nz >= DNSLAB_PAIR_MIN_NZ &&
+                                  x->g.n >= (x->Lo.esz == 8 ? DNSLAB_PAIR_MIN_CELLS64 : DNSLAB_PAIR_MIN_CELLS32));
 }
+bool mom_pairs(const dnslab_ctx* x) { return stage_pairs(x); }
 // The scalar's second pair reads c^n at the cells around its tile, so it
 // cannot write c^n in place: the pairs run when the filter is on (the RK4
 // result then goes to a work field).
-bool sca_pairs(const dnslab_ctx* x) {
-    if (x->pairs_mode == 0 || !DNSLAB_PAIRS || x->P.filter == 0 || !mom_pair_supported(x->g, x->Lo.LP)) return false;
-    return x->pairs_mode == 1 || x->Lo.LP.kc >= DNSLAB_PAIR_MIN_KC;
-}
+bool sca_pairs(const dnslab_ctx* x) { return x->P.filter != 0 && stage_pairs(x); }
 // Partial-sum slots the scalar stages fill (divergence and, without the filter, CO2).
 int sca_nblocks(const dnslab_ctx* x) { return sca_pairs(x) ? x->Lo.LP.nblocks : x->Lo.L.nblocks; }
 
