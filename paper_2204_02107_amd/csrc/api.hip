@@ -197,14 +197,6 @@ Grid make_grid(const dnslab_params* P) {
 #ifndef DNSLAB_RING_MIN_BLOCKS
 #define DNSLAB_RING_MIN_BLOCKS 1024
 #endif
-// Longer filter chunks where the 64 x DNSLAB_FROWS tiles still give this
-// many blocks.
-#ifndef DNSLAB_FKC_LONG
-#define DNSLAB_FKC_LONG 64
-#endif
-#ifndef DNSLAB_FKC_LONG_BLOCKS
-#define DNSLAB_FKC_LONG_BLOCKS 2048
-#endif
 #ifndef DNSLAB_FKC_MIN_SMALL
 #define DNSLAB_FKC_MIN_SMALL 12
 #endif
@@ -289,6 +281,17 @@ Grid make_grid(const dnslab_params* P) {
 #endif
 #ifndef DNSLAB_FILTER_SMALL_CELLS
 #define DNSLAB_FILTER_SMALL_CELLS (1LL << 21)
+#endif
+// (2 planes up to this: 64^3 FP64 filter 14 -> 12 us, FP32 13 -> 10; 128x64x64
+// 17 -> 16 and 15 -> 13)
+#ifndef DNSLAB_FILTER_TINY_CELLS
+#define DNSLAB_FILTER_TINY_CELLS (1LL << 19)
+#endif
+#ifndef DNSLAB_RING_MIN_CELLS
+#define DNSLAB_RING_MIN_CELLS (1LL << 20)      // register-ring filter (make_layout)
+#endif
+#ifndef DNSLAB_CORR_RING_CELLS
+#define DNSLAB_CORR_RING_CELLS (1LL << 21)     // and correction, above this
 #endif
 
 #ifndef DNSLAB_IB_ONLY_CELLS
@@ -422,27 +425,31 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     const int kc_min = g.n <= DNSLAB_SMALL_CELLS ? 2 : 4;
     Lo.L = stencil_launch(g, DNSLAB_ROWS, stencil_kc(g, DNSLAB_ROWS, DNSLAB_KC, kc_min), 1);
     Lo.L1 = Lo.L;
-    // Filter and correction: 64 x DNSLAB_FROWS tiles with long z chunks (the
-    // radius-3 filter re-reads 6 halo planes per chunk), their register-ring
-    // forms, where that still gives DNSLAB_RING_MIN_BLOCKS blocks; on smaller
-    // grids 64 x 8 tiles with shorter chunks, the LDS filter and the
-    // one-cell-per-thread correction, which keep many more blocks (on
-    // 192x96x64 the large tiles made the filter 28 -> 53 us and the
-    // correction 12 -> 32 us: 24 blocks for 256 CUs).
-    const int fkc_min = Lo.esz == 8 ? DNSLAB_FKC_MIN : DNSLAB_FKC_MIN32;
-    Lo.LF = stencil_launch(g, DNSLAB_FROWS,
-                           std::max(stencil_kc(g, DNSLAB_FROWS, DNSLAB_FKC), std::min(fkc_min, P->nz)), 1);
-    const bool ring_geometry = Lo.LF.nblocks >= DNSLAB_RING_MIN_BLOCKS;
-    if (ring_geometry && Lo.LF.kc < DNSLAB_FKC_LONG) {
-        const StencilLaunch lf = stencil_launch(g, DNSLAB_FROWS, std::min(DNSLAB_FKC_LONG, P->nz), 1);
-        if (lf.nblocks >= DNSLAB_FKC_LONG_BLOCKS) Lo.LF = lf;
-    }
-    if (!ring_geometry) {
-        const int small_min = Lo.esz == 8 ? DNSLAB_FKC_MIN_SMALL : DNSLAB_FKC_MIN_SMALL32;
-        if (g.n < DNSLAB_FILTER_SMALL_CELLS)
-            Lo.LF = stencil_launch(g, 4, std::min(4, P->nz), 1);
-        else
+    // Filter and correction: 64 x DNSLAB_FROWS tiles, in their register-ring
+    // forms, with the chunk by rounds of one block per CU (the radius-3 filter
+    // reads 6 planes beside its chunk).  Filter + scalar filter, FP64:
+    // 512x256x192 355 us in 96-plane chunks (one round), 373 in 48 (two), 394 in
+    // 24 (four); 256x128x96 66 in 12 (one round), 82 in 8, 73 in 64 x 8 tiles of
+    // the LDS filter; 192x96x64 40 and 42.  FP32: 256x128x96 48 in 12 and 57;
+    // 384x144x96 73 in 24 and 96; 192x96x64 32 and 33.  128x64x64 gets 64 blocks
+    // and is faster in small tiles (FP64 29 and 27).  The correction, with less
+    // to read, gains from 2^21 cells on (384x144x96 FP64 66 -> 60 us; 256x128x64
+    // 25 -> 27).
+    const bool ring_geometry = P->nx % 64 == 0 && P->ny % DNSLAB_FROWS == 0 && g.n >= DNSLAB_RING_MIN_CELLS;
+    if (ring_geometry) {
+        Lo.LF = stencil_launch(g, DNSLAB_FROWS, march_chunk(g, DNSLAB_FROWS, 6, 256, 64), 1);
+    } else if (g.n < DNSLAB_FILTER_SMALL_CELLS) {
+        Lo.LF = stencil_launch(g, 4, std::min(g.n <= DNSLAB_FILTER_TINY_CELLS ? 2 : 4, P->nz), 1);
+    } else {
+        // other grids: 64 x DNSLAB_FROWS tiles where those give enough blocks,
+        // else 64 x 8 with shorter chunks
+        const int fkc_min = Lo.esz == 8 ? DNSLAB_FKC_MIN : DNSLAB_FKC_MIN32;
+        Lo.LF = stencil_launch(g, DNSLAB_FROWS,
+                               std::max(stencil_kc(g, DNSLAB_FROWS, DNSLAB_FKC), std::min(fkc_min, P->nz)), 1);
+        if (Lo.LF.nblocks < DNSLAB_RING_MIN_BLOCKS) {
+            const int small_min = Lo.esz == 8 ? DNSLAB_FKC_MIN_SMALL : DNSLAB_FKC_MIN_SMALL32;
             Lo.LF = stencil_launch(g, 8, std::max(stencil_kc(g, 8, DNSLAB_FKC), std::min(small_min, P->nz)), 1);
+        }
     }
     {
         // Stage pairs: one FP64 block nearly fills a CU's share of the
@@ -456,7 +463,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
         Lo.LP = stencil_launch(g, DNSLAB_PROWS,
                                Lo.esz == 8 ? march_chunk(g, DNSLAB_PROWS, 4, 256, 128) : march_chunk(g, DNSLAB_PROWS, 4, 512, 64), 1);
     }
-    Lo.LC = ring_geometry ? Lo.LF : Lo.L1;
+    Lo.LC = ring_geometry && g.n > DNSLAB_CORR_RING_CELLS ? Lo.LF : Lo.L1;
     Lo.nparts = std::max(std::max(std::max(Lo.L.nblocks, Lo.L1.nblocks), Lo.LF.nblocks), Lo.LP.nblocks);
     // workspace layout
     size_t off = 0;
