@@ -258,7 +258,7 @@ Grid make_grid(const dnslab_params* P) {
 #define DNSLAB_COL_FP32_WIDE 0    // measured slower on 1024x512x256 (y 272 -> 288 us, z 382 -> 436 us)
 #endif
 #ifndef DNSLAB_PAIRS
-#define DNSLAB_PAIRS 1         // RK4 stages two at a time (fused stage pairs) where the tile divides the grid
+#define DNSLAB_PAIRS 1         // RK4 stages two at a time (fused stage pairs) where the tile fits the grid
 #endif
 #ifndef DNSLAB_PAIR_MIN_CELLS64
 #define DNSLAB_PAIR_MIN_CELLS64 (1LL << 20)   // stage pairs from this grid size on (mom_pairs)
@@ -435,7 +435,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     // and is faster in small tiles (FP64 29 and 27).  The correction, with less
     // to read, gains from 2^21 cells on (384x144x96 FP64 66 -> 60 us; 256x128x64
     // 25 -> 27).
-    const bool ring_geometry = P->nx % 64 == 0 && P->ny % DNSLAB_FROWS == 0 && g.n >= DNSLAB_RING_MIN_CELLS;
+    const bool ring_geometry = P->nx >= 64 && P->ny >= DNSLAB_FROWS && g.n >= DNSLAB_RING_MIN_CELLS;
     if (ring_geometry) {
         Lo.LF = stencil_launch(g, DNSLAB_FROWS, march_chunk(g, DNSLAB_FROWS, 6, 256, 64), 1);
     } else if (g.n < DNSLAB_FILTER_SMALL_CELLS) {
@@ -551,7 +551,7 @@ struct dnslab_ctx {
     // step n; it runs on a second stream, overlapping the pressure solves of
     // step n + 1 (see one_step).
     bool overlap;          // defer the scalar work to aux (plain contexts; not when recording)
-    int pairs_mode = -1;   // RK4 stage pairs: -1 by grid size, 0 never, 1 wherever the tile divides the grid
+    int pairs_mode = -1;   // RK4 stage pairs: -1 by grid size, 0 never, 1 wherever the tile fits the grid
     int fft_pipe_mode = -1;   // pipelined column passes: -1 by tile count, 0 never, 1 wherever they apply
     hipStream_t aux;       // created on first use
     hipEvent_t ev_fork, ev_join;
@@ -877,12 +877,13 @@ int project(dnslab_ctx* x, const T* const us[3], T* const out[3]) {
     return rc;
 }
 
-// RK4 stages two per pass where the pair kernels' tile divides the grid, it
-// has enough cells to fill the chip with pair blocks and more planes than the
+// RK4 stages two per pass where the pair kernels' tile fits the grid, it has
+// enough cells to fill the chip with pair blocks and more planes than the
 // four that a pair reads beside its own.  Momentum + scalar kernels of a step,
 // pairs / single stages: FP64 192x96x64 129 / 160 us, 128x64x64 85 / 92 (the
 // step 192 / 185: the pairs overlap less), 256x128x96 279 / 392; FP32 192x96x64
-// 103 / 100, 256x128x64 119 / 145, 384x144x96 260 / 348.  2D 1536x192 (nz = 1)
+// 103 / 100, 256x128x64 119 / 145, 384x144x96 260 / 348
+// (and 216x108x72, below the line, 115 / 130: its steps take the same time).  2D 1536x192 (nz = 1)
 // FP64: step 203 us with pairs, 170 without.
 // dnslab_set_stage_pairs overrides the choice (pairs_mode 0: never, 1:
 // wherever supported).

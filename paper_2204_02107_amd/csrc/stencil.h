@@ -185,8 +185,8 @@ template <typename T> hipError_t launch_mom_stage(int mode, const MomArgs<T>& a,
 #ifndef DNSLAB_PROWS
 #define DNSLAB_PROWS 8
 #endif
-// The pair kernels need the 64 x DNSLAB_PROWS tile to divide the grid in x
-// and y (mom_pair_supported); otherwise the single-stage kernels run.
+// The pair kernels need a grid of at least one 64 x DNSLAB_PROWS tile
+// (mom_pair_supported); otherwise the single-stage kernels run.
 bool mom_pair_supported(const Grid& g, const StencilLaunch& L);
 template <typename T> hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunch& L,
                                                  hipStream_t s, Recorder* rec = nullptr);

@@ -46,6 +46,8 @@ namespace {
 #endif
 constexpr int FILT_LDS = 16;   // filter kind mode bit: LDS-tiled variant
 constexpr int FILT_RING = 32;  // filter kind mode bit: LDS-tiled variant with register rings
+constexpr int FILT_PART = 64;  // filter kind mode bit: its form for grids that the tile does not divide
+constexpr int PAIR_PART = 2;   // stage pair kind mode bit: the same
 constexpr int STAGE_LDS = 8;   // RK4 stage kind mode bit: LDS-tiled variant
 
 constexpr double INV_PI6 = 1.0 / (3.14159265358979323846 * 3.14159265358979323846 *
@@ -58,6 +60,7 @@ struct Col {
     int dir;       // z march direction of the radius-3 filter: +1, or -1 on odd z chunks
     unsigned row, rowm, rowp;   // j*nx, jm*nx, jp*nx
     bool active;
+    bool own;      // column_tile: this block stores the column
 };
 
 // XCD-aware block order.  Workgroups are dealt to the 8 XCDs round-robin by
@@ -106,6 +109,36 @@ __device__ __forceinline__ Col column(const Grid& g, int kc, const BlockIdx3& bi
     return c;
 }
 
+// The column of a kernel that works on whole tiles (nx >= BX, ny >= BY): where
+// the tile does not divide the grid, the last tile of a row or column of tiles
+// starts early enough to end with the grid, and its cells that the tile before
+// it has too are computed but left to that one (own).  Steps on such grids
+// with these kernels against the one-cell-per-thread ones: 486x216x108 FP64 3508
+// -> 2110 us, FP32 2189 -> 1475; 324x108x72 FP64 707 -> 563; 216x108x72 486 ->
+// 406.  The stage pairs and the ring filter are compiled for both kinds of
+// grid (PART): the test around their stores costs 3% (the scalar's filter 35%)
+// on grids that the tile divides.
+__device__ __forceinline__ Col column_tile(const Grid& g, int kc, const BlockIdx3& bi) {
+    Col c;
+    int bx, by, bz;
+    logical_block(bi, bx, by, bz);
+    const int is = bx * (int)blockDim.x, js = by * (int)blockDim.y;
+    c.i = min(is, g.nx - (int)blockDim.x) + (int)threadIdx.x;
+    c.j = min(js, g.ny - (int)blockDim.y) + (int)threadIdx.y;
+    c.k0 = bz * kc;
+    c.k1 = min(c.k0 + kc, g.nz);
+    c.dir = (DNSLAB_ZALT && (bz & 1)) ? -1 : 1;
+    c.active = true;
+    c.own = c.i >= is && c.j >= js;
+    c.im = c.i == 0 ? g.nx - 1 : c.i - 1;
+    c.ip = c.i + 1 == g.nx ? 0 : c.i + 1;
+    c.jm = c.j == 0 ? g.ny - 1 : c.j - 1;
+    c.jp = c.j + 1 == g.ny ? 0 : c.j + 1;
+    c.row = (unsigned)c.j * g.nx;
+    c.rowm = (unsigned)c.jm * g.nx;
+    c.rowp = (unsigned)c.jp * g.nx;
+    return c;
+}
 
 // Courant rate |u|/dx + |v|/dy + |w|/dz in FP64, summed left to right without
 // contraction so that it rounds like a plain sequential evaluation.
@@ -217,8 +250,8 @@ __device__ __forceinline__ void mom_rhs_cell(const MomCoef<T>& cf, const T z0[3]
 template <typename T, int MODE, bool LDS>
 __device__ __forceinline__ void mom_stage_body(const MomArgs<T>& a, const BlockIdx3& bi) {
     const Grid& g = a.g;
-    const Col col = column(g, a.kc, bi);
-    if (!LDS && !col.active) return;      // the LDS variant only runs on tiles inside the grid
+    const Col col = LDS ? column_tile(g, a.kc, bi) : column(g, a.kc, bi);
+    if (!LDS && !col.active) return;
     const int k0 = col.k0, k1 = col.k1;
     const unsigned nxy = (unsigned)g.nxy;
     const T dt = (MODE == ST_RHS) ? T(0) : T(a.dtp ? *a.dtp : a.dt);
@@ -322,6 +355,7 @@ __device__ __forceinline__ void mom_stage_body(const MomArgs<T>& a, const BlockI
             // LDS variant: acc and u^n of this cell were loaded one plane ahead
             const T accv = (MODE == ST_HALF || MODE == ST_FULL || MODE == ST_LAST)
                                ? (LDS ? pa[c] : a.acc[c][idx]) : T(0);
+            if (LDS && !col.own) continue;
             if (MODE == ST_FIRST) {
                 a.acc[c][idx] = z0[c] + (dt / T(6)) * kv[c];
                 a.out[c][idx] = z0[c] + (dt / T(2)) * kv[c];
@@ -555,7 +589,7 @@ struct PlaneOffsets {
     }
 };
 
-template <typename T, int PAIR, int D, int BY>
+template <typename T, int PAIR, int D, int BY, bool PART>
 __device__ __forceinline__ void mom_pair_body(const MomPairArgs<T>& a, const BlockIdx3& bi) {
     constexpr int BX = 64;
     constexpr int U = (4 + D) & ~1;                   // ring slots: even (LDS buffer parity), >= 3 + D
@@ -565,8 +599,9 @@ __device__ __forceinline__ void mom_pair_body(const MomPairArgs<T>& a, const Blo
     constexpr int HM = (4 * (BX + 2) + 4 * BY + BX * BY - 1) / (BX * BY);   // halo cells per thread
     constexpr unsigned E = sizeof(T);
     const Grid& g = a.g;
-    const Col col = column(g, a.kc, bi);
+    const Col col = column_tile(g, a.kc, bi);
     const int k0 = col.k0, k1 = col.k1;
+    const bool own = !PART || col.own;
     const T dt = T(a.dtp ? *a.dtp : a.dt);
     const MomCoef<T> cf = mom_coef<T>(g, a.nu, a.body);
     extern __shared__ unsigned char smem_raw[];
@@ -770,13 +805,15 @@ __device__ __forceinline__ void mom_pair_body(const MomPairArgs<T>& a, const Blo
                 yp[c] = Wk[c * TW + cW + WW];
             }
             mom_rhs_cell<T>(cf, wz[S0], xm, xp, ym, yp, wz[SM], wz[S1], fq[S0], a.frc, po.p0 + cell, kv);
+            if (own) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (PAIR == 0) {
-                    bst(a.acc[c], cb, po.p0 * E, ac[S0][c] + (dt / T(3)) * kv[c]);
-                    bst(a.out[c], cb, po.p0 * E, vq[S0][c] + (dt / T(2)) * kv[c]);
-                } else {
-                    bst(a.out[c], cb, po.p0 * E, ac[S0][c] + (dt / T(6)) * kv[c]);
+                for (int c = 0; c < 3; ++c) {
+                    if (PAIR == 0) {
+                        bst(a.acc[c], cb, po.p0 * E, ac[S0][c] + (dt / T(3)) * kv[c]);
+                        bst(a.out[c], cb, po.p0 * E, vq[S0][c] + (dt / T(2)) * kv[c]);
+                    } else {
+                        bst(a.out[c], cb, po.p0 * E, ac[S0][c] + (dt / T(6)) * kv[c]);
+                    }
                 }
             }
         }
@@ -906,7 +943,7 @@ __device__ __forceinline__ void sca_stage_body(const ScaArgs<T>& a, const BlockI
 // second stage at plane K needs u, v and the flags at the same neighbours the
 // first stage read one plane earlier: each thread keeps them from there.
 // ---------------------------------------------------------------------------
-template <typename T, int PAIR, int D, int BY>
+template <typename T, int PAIR, int D, int BY, bool PART>
 __device__ __forceinline__ void sca_pair_body(const ScaPairArgs<T>& a, const BlockIdx3& bi) {
     constexpr int BX = 64;
     constexpr int U = (5 + D) & ~1;                   // ring slots: even (LDS buffer parity), >= 4 + D
@@ -916,8 +953,9 @@ __device__ __forceinline__ void sca_pair_body(const ScaPairArgs<T>& a, const Blo
     constexpr int HM = (4 * (BX + 2) + 4 * BY + BX * BY - 1) / (BX * BY);
     constexpr unsigned E = sizeof(T);
     const Grid& g = a.g;
-    const Col col = column(g, a.kc, bi);
+    const Col col = column_tile(g, a.kc, bi);
     const int k0 = col.k0, k1 = col.k1;
+    const bool own = !PART || col.own;
     const T dt = T(a.dtp ? *a.dtp : a.dt);
     const ScaCoef<T> cf = sca_coef<T>(g, a.alpha);
     extern __shared__ unsigned char smem_raw[];
@@ -1124,22 +1162,24 @@ __device__ __forceinline__ void sca_pair_body(const ScaPairArgs<T>& a, const Blo
                                         sx[S0][0], sx[S0][1], sx[S0][2], sx[S0][3], wq[SM], wq[S1], fq[S0],
                                         sf[S0][0], sf[S0][1], sf[S0][2], sf[S0][3], fq[SM], fq[S1], a.frc,
                                         po.p0 + cell);
-            if (PAIR == 0) {
-                bst(a.acc, cb, po.p0 * E, ac[S0] + (dt / T(3)) * G);
-                bst(a.out, cb, po.p0 * E, cq[S0] + (dt / T(2)) * G);
-                if (a.part.p) {
-                    const double dv = ((double)sx[S0][1] - (double)sx[S0][0]) * g.inv2d[0] +
-                                      ((double)sx[S0][3] - (double)sx[S0][2]) * g.inv2d[1] +
-                                      ((double)wq[S1] - (double)wq[SM]) * g.inv2d[2];
-                    part.div2 += dv * dv;
-                }
-            } else {
-                const T cnew = (fq[S0] & F_FLUID) ? ac[S0] + (dt / T(6)) * G : T(0);
-                bst(a.out, cb, po.p0 * E, cnew);
-                if (a.part.p) {
-                    const double b = (fq[S0] & F_FLUID) ? 1.0 : 0.0;
-                    part.mass += b * (double)cnew;
-                    if (fq[S0] & F_ROOM) { part.room_num += b * (double)cnew; part.room_den += b; }
+            if (own) {
+                if (PAIR == 0) {
+                    bst(a.acc, cb, po.p0 * E, ac[S0] + (dt / T(3)) * G);
+                    bst(a.out, cb, po.p0 * E, cq[S0] + (dt / T(2)) * G);
+                    if (a.part.p) {
+                        const double dv = ((double)sx[S0][1] - (double)sx[S0][0]) * g.inv2d[0] +
+                                          ((double)sx[S0][3] - (double)sx[S0][2]) * g.inv2d[1] +
+                                          ((double)wq[S1] - (double)wq[SM]) * g.inv2d[2];
+                        part.div2 += dv * dv;
+                    }
+                } else {
+                    const T cnew = (fq[S0] & F_FLUID) ? ac[S0] + (dt / T(6)) * G : T(0);
+                    bst(a.out, cb, po.p0 * E, cnew);
+                    if (a.part.p) {
+                        const double b = (fq[S0] & F_FLUID) ? 1.0 : 0.0;
+                        part.mass += b * (double)cnew;
+                        if (fq[S0] & F_ROOM) { part.room_num += b * (double)cnew; part.room_den += b; }
+                    }
                 }
             }
         }
@@ -1230,15 +1270,15 @@ __device__ __forceinline__ void filter_body(const FiltArgs<T>& a, const BlockIdx
 // each side, no corners) is staged in LDS per field; the interior comes from
 // the z register window, so only the halo is fetched from memory, and each
 // cell's twelve x/y neighbour loads become LDS reads.  Two tile buffers
-// alternate between planes, so one barrier per plane suffices.  Requires the
-// tile to divide the grid in x and y (nx % BX == 0, ny % BY == 0); the
-// arithmetic is that of filter_body term by term.
+// alternate between planes, so one barrier per plane suffices.  Requires a
+// grid of at least one tile (nx >= BX, ny >= BY); the arithmetic is that of
+// filter_body term by term.
 template <typename T, int NF>
 __device__ __forceinline__ void filter_lds_body(const FiltArgs<T>& a, const BlockIdx3& bi) {
     extern __shared__ unsigned char smem_raw[];
     T* lds = reinterpret_cast<T*>(smem_raw);
     const Grid& g = a.g;
-    const Col col = column(g, a.kc, bi);
+    const Col col = column_tile(g, a.kc, bi);
     const int BX = blockDim.x, BY = blockDim.y;
     const int W = BX + 6, H = BY + 6;          // tile row length and rows
     const int tsz = W * H;                     // one field's tile
@@ -1303,13 +1343,13 @@ __device__ __forceinline__ void filter_lds_body(const FiltArgs<T>& a, const Bloc
             const T dz6 = (win[f][0] + win[f][6]) - T(6) * (win[f][1] + win[f][5]) +
                           T(15) * (win[f][2] + win[f][4]) - T(20) * f0;
             res[f] = (fl & F_FLUID) ? f0 + c6 * (dx6 + dy6 + dz6) : T(0);
-            a.out[f][idx] = res[f];
+            if (col.own) a.out[f][idx] = res[f];
 #pragma unroll
             for (int m = 0; m < 6; ++m) win[f][m] = win[f][m + 1];
             win[f][6] = pf[f];
             if (left > 1) pf[f] = a.in[f][(unsigned)wrap(k + 5 * dir, g.nz) * nxy + cell];
         }
-        if (a.part.p) {
+        if (a.part.p && col.own) {
             const double b = (fl & F_FLUID) ? 1.0 : 0.0;
             if (NF == 3) {
                 const double u = (double)res[0], v = (double)res[1], w = (double)res[2];
@@ -1331,7 +1371,7 @@ __device__ __forceinline__ void filter_lds_body(const FiltArgs<T>& a, const Bloc
 // unrolled U times, and every access is a raw buffer access with a scalar
 // plane offset.  The tile is 64 x BY (compile time), so LDS offsets are
 // immediates.
-template <typename T, int NF, int BY>
+template <typename T, int NF, int BY, bool PART>
 __device__ __forceinline__ void filter_ring_body(const FiltArgs<T>& a, const BlockIdx3& bi) {
     constexpr int BX = 64, W = BX + 6, H = BY + 6, TSZ = W * H;
     constexpr int U = 8;                                   // window (7 planes) and its prefetch
@@ -1340,7 +1380,7 @@ __device__ __forceinline__ void filter_ring_body(const FiltArgs<T>& a, const Blo
     extern __shared__ unsigned char smem_raw[];
     T* const lds = reinterpret_cast<T*>(smem_raw);        // [2 planes][NF][TSZ]
     const Grid& g = a.g;
-    const Col col = column(g, a.kc, bi);
+    const Col col = column_tile(g, a.kc, bi);
     const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + BX * ty;
     const int i0 = col.i - tx, j0 = col.j - ty;
     const unsigned cell = col.row + col.i, cb = cell * E;
@@ -1427,11 +1467,11 @@ __device__ __forceinline__ void filter_ring_body(const FiltArgs<T>& a, const Blo
                           T(6) * (win[f][(P + U - 2) % U] + win[f][(P + 2) % U]) +
                           T(15) * (win[f][(P + U - 1) % U] + win[f][(P + 1) % U]) - T(20) * f0;
             res[f] = (fl & F_FLUID) ? f0 + c6 * (dx6 + dy6 + dz6) : T(0);
-            bst(a.out[f], cb, p0 * E, res[f]);
+            if (!PART || col.own) bst(a.out[f], cb, p0 * E, res[f]);
             // the window's next plane (position r + 5, into the slot of r - 3)
             win[f][(P + 5) % U] = bld(a.in[f], cb, q5 * E);
         }
-        if (a.part.p) {
+        if (a.part.p && (!PART || col.own)) {
             const double b = (fl & F_FLUID) ? 1.0 : 0.0;
             if (NF == 3) {
                 const double u = (double)res[0], v = (double)res[1], w = (double)res[2];
@@ -1529,7 +1569,7 @@ __device__ __forceinline__ void correct_ring_body(const T* const us[3], T* const
     constexpr unsigned E = sizeof(T);
     extern __shared__ unsigned char smem_raw[];
     Q* const lds = reinterpret_cast<Q*>(smem_raw);     // [2 planes][TS]
-    const Col col = column(g, kc, bi);
+    const Col col = column_tile(g, kc, bi);
     const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + BX * ty;
     const int i0 = col.i - tx, j0 = col.j - ty;
     const unsigned cell = col.row + col.i, cb = cell * E;
@@ -1602,15 +1642,17 @@ __device__ __forceinline__ void correct_ring_body(const T* const us[3], T* const
             o[0] = fluid ? (T)(u - gx) : T(0);
             o[1] = fluid ? (T)(v - gy) : T(0);
             o[2] = fluid ? (T)(w - gz) : T(0);
-            bst(pout, cell * 4u, p0 * 4u, (float)pz[P % U]);
+            if (col.own) bst(pout, cell * 4u, p0 * 4u, (float)pz[P % U]);
         } else {
             o[0] = fluid ? uq[P % U][0] - (T)gx : T(0);
             o[1] = fluid ? uq[P % U][1] - (T)gy : T(0);
             o[2] = fluid ? uq[P % U][2] - (T)gz : T(0);
         }
+        if (col.own) {
 #pragma unroll
-        for (int c = 0; c < 3; ++c) bst(out[c], cb, p0 * E, o[c]);
-        if (pa.p) {
+            for (int c = 0; c < 3; ++c) bst(out[c], cb, p0 * E, o[c]);
+        }
+        if (pa.p && col.own) {
             const double ud = (double)o[0], vd = (double)o[1], wd = (double)o[2];
             part.ke += fluid ? ud * ud + vd * vd + wd * wd : 0.0;
             part.rate = fmax(part.rate, courant_rate(ud, vd, wd, g));
@@ -1980,27 +2022,27 @@ __global__ __launch_bounds__(1024) void k_mom_stage_b(const BRec<MomArgs<T>>* __
     const MomArgs<T> a = from_table(tab[s_].a);
     mom_stage_body<T, MODE, LDS>(a, bi_);
 }
-template <typename T, int PAIR>
+template <typename T, int PAIR, bool PART>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, true, PAIR>()))) void k_mom_pair(const MomPairArgs<T> a) {
-    mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS>(a, hw_block());
+    mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS, PART>(a, hw_block());
 }
-template <typename T, int PAIR>
+template <typename T, int PAIR, bool PART>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, true, PAIR>()))) void k_mom_pair_b(const BRec<MomPairArgs<T>>* __restrict__ tab,
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
     const MomPairArgs<T> a = from_table(tab[s_].a);
-    mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS>(a, bi_);
+    mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS, PART>(a, bi_);
 }
-template <typename T, int PAIR>
+template <typename T, int PAIR, bool PART>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, false, PAIR>()))) void k_sca_pair(const ScaPairArgs<T> a) {
-    sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS>(a, hw_block());
+    sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS, PART>(a, hw_block());
 }
-template <typename T, int PAIR>
+template <typename T, int PAIR, bool PART>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, false, PAIR>()))) void k_sca_pair_b(const BRec<ScaPairArgs<T>>* __restrict__ tab,
                                                     const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
     const ScaPairArgs<T> a = from_table(tab[s_].a);
-    sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS>(a, bi_);
+    sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS, PART>(a, bi_);
 }
 template <typename T, int MODE>
 __global__ __launch_bounds__(1024) void k_sca_stage(const ScaArgs<T> a) { sca_stage_body<T, MODE>(a, hw_block()); }
@@ -2029,16 +2071,16 @@ __global__ __launch_bounds__(1024) void k_filter_lds_b(const BRec<FiltArgs<T>>* 
     const FiltArgs<T> a = from_table(tab[s_].a);
     filter_lds_body<T, NF>(a, bi_);
 }
-template <typename T, int NF>
+template <typename T, int NF, bool PART>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_filter_ring(const FiltArgs<T> a) {
-    filter_ring_body<T, NF, DNSLAB_FROWS>(a, hw_block());
+    filter_ring_body<T, NF, DNSLAB_FROWS, PART>(a, hw_block());
 }
-template <typename T, int NF>
+template <typename T, int NF, bool PART>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_filter_ring_b(const BRec<FiltArgs<T>>* __restrict__ tab,
                                                        const unsigned* __restrict__ st, int ns) {
     DNSLAB_BATCH_COORD(tab, st, ns)
     const FiltArgs<T> a = from_table(tab[s_].a);
-    filter_ring_body<T, NF, DNSLAB_FROWS>(a, bi_);
+    filter_ring_body<T, NF, DNSLAB_FROWS, PART>(a, bi_);
 }
 template <typename T>
 __global__ __launch_bounds__(1024) void k_correct(const CorrArgs<T> a) { correct_body<T>(a, hw_block()); }
@@ -2143,17 +2185,22 @@ StencilLaunch stencil_launch(const Grid& g, int rows, int kc, int cells_x) {
 }
 
 
-// The register-ring correction: 64 x DNSLAB_FROWS tiles dividing the grid.
+// The register-ring correction: 64 x DNSLAB_FROWS tiles.
 inline bool correct_ring_fits(const Grid& g, const StencilLaunch& L) {
-    return DNSLAB_CORRECT_RING && L.block.x == 64 && L.block.y == DNSLAB_FROWS && g.nx % 64 == 0 &&
-           g.ny % DNSLAB_FROWS == 0;
+    return DNSLAB_CORRECT_RING && L.block.x == 64 && L.block.y == DNSLAB_FROWS && g.nx >= 64 &&
+           g.ny >= DNSLAB_FROWS;
 }
 
-// LDS variants of the z-marching kernels need the block's tile inside the grid.
-// radius: the halo width; every thread loads at most two halo cells per field.
-inline bool tile_divides(const Grid& g, const StencilLaunch& L, int radius) {
+inline bool tile_divides(const Grid& g, const StencilLaunch& L) {
+    return g.nx % (int)L.block.x == 0 && g.ny % (int)L.block.y == 0;
+}
+
+// LDS variants of the z-marching kernels need a grid of at least one tile
+// (column_tile).  radius: the halo width; every thread loads at most two halo
+// cells per field.
+inline bool tile_fits(const Grid& g, const StencilLaunch& L, int radius) {
     const int bx = (int)L.block.x, by = (int)L.block.y;
-    return g.nx % bx == 0 && g.ny % by == 0 && 2 * radius * (bx + by) <= 2 * bx * by;
+    return g.nx >= bx && g.ny >= by && 2 * radius * (bx + by) <= 2 * bx * by;
 }
 
 template <typename T, bool LDS>
@@ -2171,7 +2218,7 @@ template <typename T>
 hipError_t launch_mom_stage(int mode, const MomArgs<T>& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
     MomArgs<T> b = a;
     b.kc = L.kc;
-    const bool use_lds = DNSLAB_STENCIL_LDS && tile_divides(a.g, L, 1);
+    const bool use_lds = DNSLAB_STENCIL_LDS && tile_fits(a.g, L, 1);
     const size_t lds = use_lds ? (size_t)2 * 3 * (L.block.x + 2) * (L.block.y + 2) * sizeof(T) : 0;
     if (rec) {
         record_launch(rec, kind_code(KK_MOM, mode | (use_lds ? STAGE_LDS : 0), sizeof(T) == 4), L.grid, L.block, lds, b);
@@ -2186,7 +2233,7 @@ bool mom_pair_supported(const Grid& g, const StencilLaunch& L) {
     const int bx = (int)L.block.x, by = (int)L.block.y;
     // at most two halo cells of V per thread (4 (BX + 2) + 4 BY of them) and
     // one ring cell per thread (2 BX + 2 BY of them)
-    return bx == 64 && by == DNSLAB_PROWS && g.nx % bx == 0 && g.ny % by == 0 && 4 * (bx + 2) + 4 * by <= 2 * bx * by &&
+    return bx == 64 && by == DNSLAB_PROWS && g.nx >= bx && g.ny >= by && 4 * (bx + 2) + 4 * by <= 2 * bx * by &&
            2 * (bx + by) <= bx * by;
 }
 
@@ -2197,11 +2244,14 @@ hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunc
     b.kc = L.kc;
     const size_t lds = (size_t)6 * ((L.block.x + 4) * (L.block.y + 4) + (L.block.x + 2) * (L.block.y + 2)) * sizeof(T);
     if (rec) {
-        record_launch(rec, kind_code(KK_MOMPAIR, pair, sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_MOMPAIR, pair | (tile_divides(a.g, L) ? 0 : PAIR_PART), sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
-    if (pair == 0) hipLaunchKernelGGL((k_mom_pair<T, 0>), L.grid, L.block, lds, s, b);
-    else hipLaunchKernelGGL((k_mom_pair<T, 1>), L.grid, L.block, lds, s, b);
+    const bool part = !tile_divides(a.g, L);
+    if (pair == 0 && !part) hipLaunchKernelGGL((k_mom_pair<T, 0, false>), L.grid, L.block, lds, s, b);
+    else if (!part) hipLaunchKernelGGL((k_mom_pair<T, 1, false>), L.grid, L.block, lds, s, b);
+    else if (pair == 0) hipLaunchKernelGGL((k_mom_pair<T, 0, true>), L.grid, L.block, lds, s, b);
+    else hipLaunchKernelGGL((k_mom_pair<T, 1, true>), L.grid, L.block, lds, s, b);
     return hipGetLastError();
 }
 
@@ -2213,11 +2263,14 @@ hipError_t launch_sca_pair(int pair, const ScaPairArgs<T>& a, const StencilLaunc
     const size_t tv = (size_t)(L.block.x + 4) * (L.block.y + 4), tw = (size_t)(L.block.x + 2) * (L.block.y + 2);
     const size_t lds = (6 * tv + 2 * tw) * sizeof(T) + 2 * tv;
     if (rec) {
-        record_launch(rec, kind_code(KK_SCAPAIR, pair, sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_SCAPAIR, pair | (tile_divides(a.g, L) ? 0 : PAIR_PART), sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
-    if (pair == 0) hipLaunchKernelGGL((k_sca_pair<T, 0>), L.grid, L.block, lds, s, b);
-    else hipLaunchKernelGGL((k_sca_pair<T, 1>), L.grid, L.block, lds, s, b);
+    const bool part = !tile_divides(a.g, L);
+    if (pair == 0 && !part) hipLaunchKernelGGL((k_sca_pair<T, 0, false>), L.grid, L.block, lds, s, b);
+    else if (!part) hipLaunchKernelGGL((k_sca_pair<T, 1, false>), L.grid, L.block, lds, s, b);
+    else if (pair == 0) hipLaunchKernelGGL((k_sca_pair<T, 0, true>), L.grid, L.block, lds, s, b);
+    else hipLaunchKernelGGL((k_sca_pair<T, 1, true>), L.grid, L.block, lds, s, b);
     return hipGetLastError();
 }
 
@@ -2243,20 +2296,23 @@ template <typename T>
 hipError_t launch_filter(const FiltArgs<T>& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
     FiltArgs<T> b = a;
     b.kc = L.kc;
-    // the LDS-tiled variant when the tile divides the grid in x and y; its
-    // register-ring form for the 64 x DNSLAB_FROWS tile
-    const bool use_lds = DNSLAB_FILTER_LDS && tile_divides(a.g, L, 3);
+    // the LDS-tiled variant when a tile fits the grid; its register-ring form
+    // for the 64 x DNSLAB_FROWS tile
+    const bool use_lds = DNSLAB_FILTER_LDS && tile_fits(a.g, L, 3);
     const bool use_ring = use_lds && DNSLAB_FILTER_RING && L.block.x == 64 && L.block.y == DNSLAB_FROWS;
     const int nf = a.nf == 3 ? 3 : 1;
+    const bool part = use_ring && !tile_divides(a.g, L);
     const size_t lds = use_lds ? (size_t)2 * nf * (L.block.x + 6) * (L.block.y + 6) * sizeof(T) : 0;
     if (rec) {
-        record_launch(rec, kind_code(KK_FILT, (a.nf == 3 ? 3 : 1) | (use_lds ? FILT_LDS : 0) | (use_ring ? FILT_RING : 0),
-                                     sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_FILT, nf | (use_lds ? FILT_LDS : 0) | (use_ring ? FILT_RING : 0) |
+                                     (part ? FILT_PART : 0), sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
     if (use_ring) {
-        if (a.nf == 3) hipLaunchKernelGGL((k_filter_ring<T, 3>), L.grid, L.block, lds, s, b);
-        else hipLaunchKernelGGL((k_filter_ring<T, 1>), L.grid, L.block, lds, s, b);
+        if (nf == 3 && !part) hipLaunchKernelGGL((k_filter_ring<T, 3, false>), L.grid, L.block, lds, s, b);
+        else if (!part) hipLaunchKernelGGL((k_filter_ring<T, 1, false>), L.grid, L.block, lds, s, b);
+        else if (nf == 3) hipLaunchKernelGGL((k_filter_ring<T, 3, true>), L.grid, L.block, lds, s, b);
+        else hipLaunchKernelGGL((k_filter_ring<T, 1, true>), L.grid, L.block, lds, s, b);
     } else if (use_lds) {
         if (a.nf == 3) hipLaunchKernelGGL((k_filter_lds<T, 3>), L.grid, L.block, lds, s, b);
         else hipLaunchKernelGGL((k_filter_lds<T, 1>), L.grid, L.block, lds, s, b);
@@ -2376,14 +2432,18 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
         }
         case KK_MOMPAIR: {
             auto t = (const BRec<MomPairArgs<T>>*)tab;
-            if (mode == 0) hipLaunchKernelGGL((k_mom_pair_b<T, 0>), grid, blk, lds, s, t, st, ns);
-            else hipLaunchKernelGGL((k_mom_pair_b<T, 1>), grid, blk, lds, s, t, st, ns);
+            if (mode == 0) hipLaunchKernelGGL((k_mom_pair_b<T, 0, false>), grid, blk, lds, s, t, st, ns);
+            else if (mode == 1) hipLaunchKernelGGL((k_mom_pair_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
+            else if (mode == PAIR_PART) hipLaunchKernelGGL((k_mom_pair_b<T, 0, true>), grid, blk, lds, s, t, st, ns);
+            else hipLaunchKernelGGL((k_mom_pair_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
             break;
         }
         case KK_SCAPAIR: {
             auto t = (const BRec<ScaPairArgs<T>>*)tab;
-            if (mode == 0) hipLaunchKernelGGL((k_sca_pair_b<T, 0>), grid, blk, lds, s, t, st, ns);
-            else hipLaunchKernelGGL((k_sca_pair_b<T, 1>), grid, blk, lds, s, t, st, ns);
+            if (mode == 0) hipLaunchKernelGGL((k_sca_pair_b<T, 0, false>), grid, blk, lds, s, t, st, ns);
+            else if (mode == 1) hipLaunchKernelGGL((k_sca_pair_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
+            else if (mode == PAIR_PART) hipLaunchKernelGGL((k_sca_pair_b<T, 0, true>), grid, blk, lds, s, t, st, ns);
+            else hipLaunchKernelGGL((k_sca_pair_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
             break;
         }
         case KK_SCA: {
@@ -2401,8 +2461,11 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
             auto t = (const BRec<FiltArgs<T>>*)tab;
             const bool three = (mode & 7) == 3;
             if (mode & FILT_RING) {
-                if (three) hipLaunchKernelGGL((k_filter_ring_b<T, 3>), grid, blk, lds, s, t, st, ns);
-                else hipLaunchKernelGGL((k_filter_ring_b<T, 1>), grid, blk, lds, s, t, st, ns);
+                const bool part = mode & FILT_PART;
+                if (three && !part) hipLaunchKernelGGL((k_filter_ring_b<T, 3, false>), grid, blk, lds, s, t, st, ns);
+                else if (!part) hipLaunchKernelGGL((k_filter_ring_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
+                else if (three) hipLaunchKernelGGL((k_filter_ring_b<T, 3, true>), grid, blk, lds, s, t, st, ns);
+                else hipLaunchKernelGGL((k_filter_ring_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
             } else if (mode & FILT_LDS) {
                 if (three) hipLaunchKernelGGL((k_filter_lds_b<T, 3>), grid, blk, lds, s, t, st, ns);
                 else hipLaunchKernelGGL((k_filter_lds_b<T, 1>), grid, blk, lds, s, t, st, ns);
