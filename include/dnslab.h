@@ -307,7 +307,8 @@ int dnslab_set_overlap(dnslab_ctx* ctx, int32_t enable);
  * pair).  mode -1 (the default): by grid size (from 2^20 cells in FP64 and
  * 2^21 in the FP32 form, nz >= 4); 0: never (one kernel
  * per stage); 1: wherever a 64 x 8 tile fits the grid (nx >= 64,
- * ny >= 8).  The scalar's pairs also need the filter on.  Results agree
+ * ny >= 8).  Without the filter the pool keeps
+ * the scalar's single stages.  Results agree
  * to rounding (every value is computed with the same expressions).  Enqueues
  * any deferred scalar work first.  DNSLAB_EINVAL unless mode is -1, 0 or 1. */
 int dnslab_set_stage_pairs(dnslab_ctx* ctx, int32_t mode);

@@ -242,7 +242,7 @@ class Solver:
 
     def set_stage_pairs(self, mode: int):
         """RK4 stages two per pass: -1 by grid size (the default), 0 never,
-        1 wherever the 64 x 8 tile divides the grid."""
+        1 wherever a 64 x 8 tile fits the grid."""
         self._check(self.lib.dnslab_set_stage_pairs(self.ctx, int(mode)))
 
     def set_fft_pipeline(self, mode: int):

@@ -894,9 +894,10 @@ bool stage_pairs(const dnslab_ctx* x) {
 }
 bool mom_pairs(const dnslab_ctx* x) { return stage_pairs(x); }
 // The scalar's second pair reads c^n at the cells around its tile, so it
-// cannot write c^n in place: the pairs run when the filter is on (the RK4
-// result then goes to a work field).
-bool sca_pairs(const dnslab_ctx* x) { return x->P.filter != 0 && stage_pairs(x); }
+// cannot write c^n in place: its result goes to a work field, from which the
+// scalar filter or, without it, a copy takes it to c (FP32 384x144x96: scalar
+// step 126 us with single stages, 118 with pairs and the copy).
+bool sca_pairs(const dnslab_ctx* x) { return (x->P.filter != 0 || !x->rec) && stage_pairs(x); }
 // Partial-sum slots the scalar stages fill (divergence and, without the filter, CO2).
 int sca_nblocks(const dnslab_ctx* x) { return sca_pairs(x) ? x->Lo.LP.nblocks : x->Lo.L.nblocks; }
 
@@ -917,9 +918,9 @@ int scalar_rk4(dnslab_ctx* x, const T* const uvel[3], const double* dtp, double 
     s.g = x->g;
     s.acc = CA;
     const StencilLaunch& L = x->Lo.L;
-    if (sca_pairs(x) && (const void*)cout != (const void*)C) {
+    if (sca_pairs(x)) {
         // two stages per pass: c^n -> acc after stage 2 (CA) and c2 (CS1);
-        // then c2, c^n and acc -> c*
+        // then c2, c^n and acc -> c* (CS2)
         ScaPairArgs<T> q = {};
         for (int a = 0; a < 3; ++a) q.u[a] = uvel[a];
         q.flags = s.flags;
@@ -930,8 +931,9 @@ int scalar_rk4(dnslab_ctx* x, const T* const uvel[3], const double* dtp, double 
         q.g = s.g;
         q.cin = C; q.acc = CA; q.out = CS1; q.part = pdiv;
         LAUNCH(x, K_SCAP, launch_sca_pair<T>(0, q, x->Lo.LP, x->cur, x->rec));
-        q.cin = CS1; q.cn = C; q.accin = CA; q.acc = nullptr; q.out = cout; q.part = psca;
+        q.cin = CS1; q.cn = C; q.accin = CA; q.acc = nullptr; q.out = CS2; q.part = psca;
         LAUNCH(x, K_SCAP, launch_sca_pair<T>(1, q, x->Lo.LP, x->cur, x->rec));
+        if (cout != CS2) LAUNCH(x, K_SCA, launch_copy<T>(CS2, cout, x->g.n, x->cur));
         return DNSLAB_OK;
     }
     s.cs = C; s.out = CS1; s.part = pdiv;

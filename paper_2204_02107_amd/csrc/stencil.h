@@ -165,6 +165,9 @@ struct StencilLaunch {
 // cells_x: cells per thread along x (1, or 2 for the pair kernels).
 StencilLaunch stencil_launch(const Grid& g, int rows, int kc, int cells_x);
 
+// to = from, n values.
+template <typename T> hipError_t launch_copy(const T* from, T* to, long long n, hipStream_t s);
+
 // The segment table of the n sorted cell indices idx (device memory).
 hipError_t launch_forced_segs(const long long* idx, int n, ForcedSeg* seg, hipStream_t s);
 

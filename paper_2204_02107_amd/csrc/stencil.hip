@@ -2002,6 +2002,19 @@ __device__ __forceinline__ DiagArgs from_table(const DiagArgs& t) {
     return a;
 }
 
+// Four values per thread, a block's width apart.
+template <typename T>
+__global__ __launch_bounds__(256) void k_copy(const T* __restrict__ from, T* __restrict__ to, long long n) {
+    const long long b = (long long)blockIdx.x * 1024 + threadIdx.x;
+    T v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (b + 256 * q < n) v[q] = from[b + 256 * q];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        if (b + 256 * q < n) to[b + 256 * q] = v[q];
+}
+
 // The first entry of each segment writes the segment's record.
 __global__ __launch_bounds__(256) void k_forced_segs(const long long* __restrict__ idx, int n, ForcedSeg* __restrict__ seg) {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2518,6 +2531,12 @@ hipError_t launch_batched_stencil(int kind, const void* tab, const unsigned* st,
                 : batched_typed<double>(base, mode, tab, st, ns, nb, blk, lds, s);
 }
 
+template <typename T>
+hipError_t launch_copy(const T* from, T* to, long long n, hipStream_t s) {
+    hipLaunchKernelGGL((k_copy<T>), dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, s, from, to, n);
+    return hipGetLastError();
+}
+
 hipError_t launch_forced_segs(const long long* idx, int n, ForcedSeg* seg, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_forced_segs, dim3((n + 255) / 256), dim3(256), 0, s, idx, n, seg);
@@ -2536,6 +2555,7 @@ hipError_t launch_set_rate(PartSoA part, int np, StepScalars* sc, hipStream_t s)
     template hipError_t launch_sca_pair<T>(int, const ScaPairArgs<T>&, const StencilLaunch&, hipStream_t, Recorder*); \
     template hipError_t launch_filter<T>(const FiltArgs<T>&, const StencilLaunch&, hipStream_t, Recorder*);        \
     template hipError_t launch_correct<T>(const CorrArgs<T>&, const StencilLaunch&, hipStream_t, Recorder*);       \
+    template hipError_t launch_copy<T>(const T*, T*, long long, hipStream_t);                                     \
     template hipError_t launch_div<T>(const DivArgs<T>&, const StencilLaunch&, hipStream_t, Recorder*);            \
     template hipError_t launch_rate<T>(const T*, const T*, const T*, const Grid&, PartSoA,                        \
                                        const StencilLaunch&, hipStream_t);
