@@ -239,14 +239,8 @@ Grid make_grid(const dnslab_params* P) {
 #ifndef DNSLAB_YZ_MAX_PLANE32
 #define DNSLAB_YZ_MAX_PLANE32 16384   // the same for the FP32 form (1024-thread blocks)
 #endif
-#ifndef DNSLAB_FORK_EARLY_CELLS
-#define DNSLAB_FORK_EARLY_CELLS (1LL << 23)   // FP64: from this grid size the scalar half forks before the momentum stages
-#endif
-#ifndef DNSLAB_SERIAL_CELLS64
-#define DNSLAB_SERIAL_CELLS64 (1LL << 26)     // FP64: from this grid size a step runs on one stream
-#endif
-#ifndef DNSLAB_FORK_EARLY_CELLS32
-#define DNSLAB_FORK_EARLY_CELLS32 (1LL << 23)   // the same for the FP32 form
+#ifndef DNSLAB_SERIAL_CELLS
+#define DNSLAB_SERIAL_CELLS (1LL << 26)     // from this grid size a step runs on one stream
 #endif
 #ifndef DNSLAB_OVERLAP
 #define DNSLAB_OVERLAP 1       // run the scalar half of a step on a second stream
@@ -1041,7 +1035,8 @@ int ensure_aux(dnslab_ctx* x) {
 // velocity filter and the step advance (t, step, next dt from the new Courant
 // rate).  Scalar half: see scalar_half.  On a plain context the scalar half of
 // step n is enqueued on the second stream once div u* of step n + 1 is
-// enqueued (on large grids: before the momentum stages of step n + 1), so
+// enqueued (where stages run in pairs: before the momentum stages of step
+// n + 1), so
 // that it runs beside that step's work; the correction of step n + 1, which
 // overwrites the projected velocity the scalar half reads, waits for it.
 // When recording for the pool both halves go, in order, into one sequence.
@@ -1049,8 +1044,8 @@ template <typename T>
 int one_step(dnslab_ctx* x) {
     int rc = ensure_rate<T>(x);
     if (rc) return rc;
-    // (FP64 on the largest grids: one stream, see below)
-    const bool defer = x->overlap && !x->rec && !(sizeof(T) == 8 && x->g.n >= DNSLAB_SERIAL_CELLS64);
+    // (the largest grids: one stream, see below)
+    const bool defer = x->overlap && !x->rec && x->g.n < DNSLAB_SERIAL_CELLS;
     if (defer) {
         rc = ensure_aux(x);
         if (rc) return rc;
@@ -1073,21 +1068,16 @@ int one_step(dnslab_ctx* x) {
     // next stage evaluates F on it; the accumulator sums the k's as usual.
     const bool per_stage = x->P.project_each_stage != 0;
     bool forked = false;
-    // Where the scalar half of the last step forks: after div u* its work
-    // overlaps the pressure solves only, whose passes leave the memory system
-    // idle between their load and store phases (best when the solves are
-    // long against the scalar half: the 256x128x96 room loses 7% forking
-    // earlier).  On large grids the solves run closer to the bandwidth and
-    // the scalar half outlasts them, stalling the correction that waits for
-    // it, so there it forks before the momentum stages (FP32 512x256x192
-    // +2.9%, 1024x512x256 +0.5%; FP64 512x256x192 5.53 -> 5.66
-    // Gcell-steps/s).  On 1024x512x256 in FP64, where every kernel fills
-    // the GPU many times over, one stream is faster still (5.84 forking
-    // late, 5.69 early, 5.93 on one stream); in the FP32 form, whose scalar
-    // pair leaves room on the CUs for the momentum pair beside it, two
-    // streams stay faster (8.61 against 8.50).
-    const long long fork_early = sizeof(T) == 8 ? DNSLAB_FORK_EARLY_CELLS : DNSLAB_FORK_EARLY_CELLS32;
-    if (defer && x->g.n >= fork_early) {
+    // Where the scalar half of the last step forks.  Before the momentum
+    // stages where those run in pairs, whose blocks leave issue slots and
+    // bandwidth free: steps forking there / after div u* / on one stream, FP64
+    // 192x96x64 281 / 291 / 306 us, 256x128x96 561 / 579 / 601, 512x256x192 3523 /
+    // 3563 / 3573; FP32 256x128x96 403 / 420 / 440, 512x256x192 2458 / 2508 / 2485.
+    // After div u*, beside the pressure solves, on smaller grids (FP32
+    // 192x96x64 264 / 254 / 275; 64^3 the same).  On 1024x512x256, where every
+    // kernel fills the GPU many times over, one stream is fastest (FP64 21.8 /
+    // 21.3 / 21.0 ms, FP32 14.02 / 13.83 / 13.79).
+    if (defer && mom_pairs(x)) {
         rc = flush_scalar_half<T>(x);
         if (rc) return rc;
         forked = true;
