@@ -361,6 +361,7 @@ def kernel_key(sym):
     if not m:
         return None
     base, targs = m.group(1), (m.group(4) or "")
+    parts = [x.strip() for x in targs.split(",")]
     if base == "mom_stage":
         return "mom_stage"
     if base == "mom_pair":
@@ -370,14 +371,15 @@ def kernel_key(sym):
     if base == "sca_stage":
         return "scalar_stage"
     if base in ("filter", "filter_lds", "filter_ring"):
-        return "filter" if targs.endswith("3") else "filter_c"
+        return "filter" if parts[1:2] == ["3"] else "filter_c"
     if base == "fft_cols":
-        parts = [x.strip() for x in targs.split(",")]
         return "fft_z" if len(parts) > 1 and parts[1] == "2" else "fft_y"
     if base in ("fft_yz", "split_z"):
         return "fft_yz"
-    if base in ("split_x_fwd", "split_x_inv"):
-        return "fft_x_" + base[8:]
+    if base in ("split_x_fwd", "split_x_inv", "line_x_fwd", "line_x_inv"):
+        return "fft_x_" + base[-3:]
+    if base == "line_cols":
+        return "fft_z" if parts[2:3] == ["2"] else "fft_y"
     if base in ("correct", "refine_correct", "correct_ring", "refine_correct_ring"):
         return "correct"
     if base in ("div", "fft_x_fwd", "fft_x_inv", "ib_rhs", "refine_res", "refine_res_ib"):
