@@ -115,8 +115,9 @@ typedef struct {
 
 /* Bytes of device workspace a context with these parameters allocates (for
  * HBM-budget admission), not counting the list of cells next to a solid that
- * dnslab_init builds from the mask (at most 13 bytes per such cell).
- * Host-only; enqueues nothing. */
+ * dnslab_init builds from the mask (at most 13 bytes per such cell) and the
+ * forcing (40 bytes per forced cell, and a quarter byte per cell of the grid
+ * if there is any).  Host-only; enqueues nothing. */
 int dnslab_workspace_bytes(const dnslab_params* params, size_t* out_bytes);
 
 /* Create a context bound to caller-owned state buffers u, v, w, p, c (device,
