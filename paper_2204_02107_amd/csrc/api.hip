@@ -429,7 +429,8 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     // and is faster in small tiles (FP64 29 and 27).  The correction, with less
     // to read, gains from 2^21 cells on (384x144x96 FP64 66 -> 60 us; 256x128x64
     // 25 -> 27).
-    const bool ring_geometry = P->nx >= 64 && P->ny >= DNSLAB_FROWS && g.n >= DNSLAB_RING_MIN_CELLS;
+    const bool ring_geometry = P->nx >= 64 && P->ny >= DNSLAB_FROWS && g.n >= DNSLAB_RING_MIN_CELLS &&
+                               ring_offsets_fit(g, Lo.esz);
     if (ring_geometry) {
         Lo.LF = stencil_launch(g, DNSLAB_FROWS, march_chunk(g, DNSLAB_FROWS, 6, 256, 64), 1);
     } else if (g.n < DNSLAB_FILTER_SMALL_CELLS) {
@@ -882,7 +883,7 @@ int project(dnslab_ctx* x, const T* const us[3], T* const out[3]) {
 // dnslab_set_stage_pairs overrides the choice (pairs_mode 0: never, 1:
 // wherever supported).
 bool stage_pairs(const dnslab_ctx* x) {
-    if (x->pairs_mode == 0 || !DNSLAB_PAIRS || !mom_pair_supported(x->g, x->Lo.LP)) return false;
+    if (x->pairs_mode == 0 || !DNSLAB_PAIRS || !mom_pair_supported(x->g, x->Lo.LP, x->Lo.esz)) return false;
     return x->pairs_mode == 1 || (x->g.nz >= DNSLAB_PAIR_MIN_NZ &&
                                   x->g.n >= (x->Lo.esz == 8 ? DNSLAB_PAIR_MIN_CELLS64 : DNSLAB_PAIR_MIN_CELLS32));
 }

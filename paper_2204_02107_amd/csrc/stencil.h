@@ -188,9 +188,21 @@ template <typename T> hipError_t launch_mom_stage(int mode, const MomArgs<T>& a,
 #ifndef DNSLAB_PROWS
 #define DNSLAB_PROWS 8
 #endif
-// The pair kernels need a grid of at least one 64 x DNSLAB_PROWS tile
-// (mom_pair_supported); otherwise the single-stage kernels run.
-bool mom_pair_supported(const Grid& g, const StencilLaunch& L);
+// The register-ring kernels (stage pairs, filter, correction) reach a field of
+// esz-byte values through 32-bit byte offsets from its start, in a resource of
+// 2^32 - 1 bytes: fields of less than 4 GiB (2^29 cells in FP64, 2^30 in the
+// FP32 form).  At 4 GiB the last value is out of the resource's range, and
+// beyond the offsets wrap onto the first planes.  The other kernels count cells.
+inline bool ring_offsets_fit(const Grid& g, size_t esz) {
+    return (unsigned long long)g.n * esz < 1ull << 32;
+}
+// The pair kernels need a grid of at least one 64 x DNSLAB_PROWS tile, the ring
+// forms of the filter and the correction one of 64 x DNSLAB_FROWS, and all of
+// them ring_offsets_fit; otherwise the single-stage kernels and the other
+// forms run.
+bool mom_pair_supported(const Grid& g, const StencilLaunch& L, size_t esz);
+bool filter_ring_supported(const Grid& g, const StencilLaunch& L, size_t esz);
+bool correct_ring_supported(const Grid& g, const StencilLaunch& L, size_t esz);
 template <typename T> hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunch& L,
                                                  hipStream_t s, Recorder* rec = nullptr);
 template <typename T> hipError_t launch_sca_pair(int pair, const ScaPairArgs<T>& a, const StencilLaunch& L,

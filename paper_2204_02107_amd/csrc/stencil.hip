@@ -523,7 +523,8 @@ __device__ __forceinline__ bool pair_phases(std::integer_sequence<int, Is...>, F
 // (one vector register, fixed for the whole march), and the address is
 // formed by the memory unit: no per-lane 64-bit address arithmetic, and
 // nothing the compiler can hoist into one 64-bit pointer per array and lane.
-// The resource does no range clipping (every offset is inside its array).
+// The resource does no range clipping: every offset is inside its array, and
+// the array inside the 2^32 - 1 bytes of the resource (ring_offsets_fit).
 typedef unsigned u32x2_t __attribute__((__vector_size__(2 * sizeof(unsigned))));
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_res(const void* p) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, -1, 0x00020000);
@@ -2199,9 +2200,9 @@ StencilLaunch stencil_launch(const Grid& g, int rows, int kc, int cells_x) {
 
 
 // The register-ring correction: 64 x DNSLAB_FROWS tiles.
-inline bool correct_ring_fits(const Grid& g, const StencilLaunch& L) {
+bool correct_ring_supported(const Grid& g, const StencilLaunch& L, size_t esz) {
     return DNSLAB_CORRECT_RING && L.block.x == 64 && L.block.y == DNSLAB_FROWS && g.nx >= 64 &&
-           g.ny >= DNSLAB_FROWS;
+           g.ny >= DNSLAB_FROWS && ring_offsets_fit(g, esz);
 }
 
 inline bool tile_divides(const Grid& g, const StencilLaunch& L) {
@@ -2214,6 +2215,11 @@ inline bool tile_divides(const Grid& g, const StencilLaunch& L) {
 inline bool tile_fits(const Grid& g, const StencilLaunch& L, int radius) {
     const int bx = (int)L.block.x, by = (int)L.block.y;
     return g.nx >= bx && g.ny >= by && 2 * radius * (bx + by) <= 2 * bx * by;
+}
+
+bool filter_ring_supported(const Grid& g, const StencilLaunch& L, size_t esz) {
+    return DNSLAB_FILTER_LDS && DNSLAB_FILTER_RING && tile_fits(g, L, 3) && L.block.x == 64 &&
+           L.block.y == DNSLAB_FROWS && ring_offsets_fit(g, esz);
 }
 
 template <typename T, bool LDS>
@@ -2242,17 +2248,17 @@ hipError_t launch_mom_stage(int mode, const MomArgs<T>& a, const StencilLaunch& 
     return hipGetLastError();
 }
 
-bool mom_pair_supported(const Grid& g, const StencilLaunch& L) {
+bool mom_pair_supported(const Grid& g, const StencilLaunch& L, size_t esz) {
     const int bx = (int)L.block.x, by = (int)L.block.y;
     // at most two halo cells of V per thread (4 (BX + 2) + 4 BY of them) and
     // one ring cell per thread (2 BX + 2 BY of them)
     return bx == 64 && by == DNSLAB_PROWS && g.nx >= bx && g.ny >= by && 4 * (bx + 2) + 4 * by <= 2 * bx * by &&
-           2 * (bx + by) <= bx * by;
+           2 * (bx + by) <= bx * by && ring_offsets_fit(g, esz);
 }
 
 template <typename T>
 hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
-    if (!mom_pair_supported(a.g, L) || (pair != 0 && pair != 1)) return hipErrorInvalidValue;
+    if (!mom_pair_supported(a.g, L, sizeof(T)) || (pair != 0 && pair != 1)) return hipErrorInvalidValue;
     MomPairArgs<T> b = a;
     b.kc = L.kc;
     const size_t lds = (size_t)6 * ((L.block.x + 4) * (L.block.y + 4) + (L.block.x + 2) * (L.block.y + 2)) * sizeof(T);
@@ -2270,7 +2276,7 @@ hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunc
 
 template <typename T>
 hipError_t launch_sca_pair(int pair, const ScaPairArgs<T>& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
-    if (!mom_pair_supported(a.g, L) || (pair != 0 && pair != 1)) return hipErrorInvalidValue;
+    if (!mom_pair_supported(a.g, L, sizeof(T)) || (pair != 0 && pair != 1)) return hipErrorInvalidValue;
     ScaPairArgs<T> b = a;
     b.kc = L.kc;
     const size_t tv = (size_t)(L.block.x + 4) * (L.block.y + 4), tw = (size_t)(L.block.x + 2) * (L.block.y + 2);
@@ -2310,9 +2316,9 @@ hipError_t launch_filter(const FiltArgs<T>& a, const StencilLaunch& L, hipStream
     FiltArgs<T> b = a;
     b.kc = L.kc;
     // the LDS-tiled variant when a tile fits the grid; its register-ring form
-    // for the 64 x DNSLAB_FROWS tile
+    // for the 64 x DNSLAB_FROWS tile and fields of less than 4 GiB
     const bool use_lds = DNSLAB_FILTER_LDS && tile_fits(a.g, L, 3);
-    const bool use_ring = use_lds && DNSLAB_FILTER_RING && L.block.x == 64 && L.block.y == DNSLAB_FROWS;
+    const bool use_ring = filter_ring_supported(a.g, L, sizeof(T));
     const int nf = a.nf == 3 ? 3 : 1;
     const bool part = use_ring && !tile_divides(a.g, L);
     const size_t lds = use_lds ? (size_t)2 * nf * (L.block.x + 6) * (L.block.y + 6) * sizeof(T) : 0;
@@ -2340,7 +2346,7 @@ template <typename T>
 hipError_t launch_correct(const CorrArgs<T>& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
     CorrArgs<T> b = a;
     b.kc = L.kc;
-    const bool ring = correct_ring_fits(a.g, L);
+    const bool ring = correct_ring_supported(a.g, L, sizeof(T));
     const size_t lds = ring ? (size_t)2 * (L.block.x + 2) * (L.block.y + 2) * sizeof(T) : 0;
     if (rec) {
         record_launch(rec, kind_code(KK_CORR, ring ? 1 : 0, sizeof(T) == 4), L.grid, L.block, lds, b);
@@ -2387,7 +2393,7 @@ hipError_t launch_refine_res(const RefineResArgs& a, const StencilLaunch& L, hip
 hipError_t launch_refine_correct(const RefineCorrArgs& a, const StencilLaunch& L, hipStream_t s, Recorder* rec) {
     RefineCorrArgs b = a;
     b.kc = L.kc;
-    const bool ring = correct_ring_fits(a.g, L);
+    const bool ring = correct_ring_supported(a.g, L, sizeof(float));
     const size_t lds = ring ? (size_t)2 * (L.block.x + 2) * (L.block.y + 2) * sizeof(double) : 0;
     if (rec) {
         record_launch(rec, kind_code(KK_REFCORR, ring ? 1 : 0, 1), L.grid, L.block, lds, b);
