@@ -109,7 +109,8 @@ struct Layout {
     StencilLaunch L;       // momentum and scalar stage kernels
     StencilLaunch L1;      // one-cell-per-thread kernels (div, refinement residual, rate)
     StencilLaunch LC;      // the velocity correction (64 x DNSLAB_FROWS tiles: its register-ring form)
-    StencilLaunch LF;      // filter
+    StencilLaunch LF;      // filter of the three velocity components
+    StencilLaunch LF1;     // filter of one field (the scalar)
     StencilLaunch LP;      // fused RK4 stage pairs
     int need;              // iterates that only the immersed-boundary term reads are written there only
     int seg_lg;            // cells per segment of the words of cells the immersed-boundary term reads
@@ -446,6 +447,15 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
             Lo.LF = stencil_launch(g, 8, std::max(stencil_kc(g, 8, DNSLAB_FKC), std::min(small_min, P->nz)), 1);
         }
     }
+    // One field in FP32 takes so little of a CU that two blocks share it, down to
+    // 8 planes a chunk: 512x256x192 53 us in 48 planes (two blocks per CU), 64 in
+    // 96 (one); 512x512x256 141 in 128, 182 in 256; 256x256x128 22 in 16, 25 in
+    // 32; but 256x128x96 12 in 12 (one) and 14 in 8.  In FP64 512x256x192 93 and 94.
+    Lo.LF1 = Lo.LF;
+    if (ring_geometry && Lo.esz == 4) {
+        const int kc = march_chunk(g, DNSLAB_FROWS, 6, 512, 64);
+        if (kc >= 8) Lo.LF1 = stencil_launch(g, DNSLAB_FROWS, kc, 1);
+    }
     {
         // Stage pairs: one FP64 block nearly fills a CU's share of the
         // bandwidth, FP32 blocks only two at a time.  Two momentum and two scalar
@@ -459,7 +469,7 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
                                Lo.esz == 8 ? march_chunk(g, DNSLAB_PROWS, 4, 256, 128) : march_chunk(g, DNSLAB_PROWS, 4, 512, 64), 1);
     }
     Lo.LC = ring_geometry && g.n > DNSLAB_CORR_RING_CELLS ? Lo.LF : Lo.L1;
-    Lo.nparts = std::max(std::max(std::max(Lo.L.nblocks, Lo.L1.nblocks), Lo.LF.nblocks), Lo.LP.nblocks);
+    Lo.nparts = std::max({Lo.L.nblocks, Lo.L1.nblocks, Lo.LF.nblocks, Lo.LF1.nblocks, Lo.LP.nblocks});
     // workspace layout
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
@@ -983,12 +993,12 @@ int scalar_half(dnslab_ctx* x) {
         fa.flags = x->flags;
         fa.g = x->g;
         fa.part = x->part;
-        LAUNCH(x, K_FILTC, launch_filter<T>(fa, x->Lo.LF, x->cur, x->rec));
+        LAUNCH(x, K_FILTC, launch_filter<T>(fa, x->Lo.LF1, x->cur, x->rec));
     }
     DiagArgs d;
     d.part = x->part;
     d.np_vel = filt ? x->Lo.LF.nblocks : x->Lo.LC.nblocks;
-    d.np_sca = filt ? x->Lo.LF.nblocks : sca_nblocks(x);
+    d.np_sca = filt ? x->Lo.LF1.nblocks : sca_nblocks(x);
     d.np_div = sca_nblocks(x);
     d.sc = x->sc;
     d.ring = x->ring;
@@ -1373,7 +1383,7 @@ int filt1(dnslab_ctx* x, const void* f, void* out) {
     a.nf = 1;
     a.flags = x->flags;
     a.g = x->g;
-    LAUNCH(x, K_FILT, launch_filter<T>(a, x->Lo.LF, x->cur, x->rec));
+    LAUNCH(x, K_FILT, launch_filter<T>(a, x->Lo.LF1, x->cur, x->rec));
     return DNSLAB_OK;
 }
 }  // namespace
