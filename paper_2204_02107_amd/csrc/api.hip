@@ -901,7 +901,9 @@ bool mom_pairs(const dnslab_ctx* x) { return stage_pairs(x); }
 // The scalar's second pair reads c^n at the cells around its tile, so it
 // cannot write c^n in place: its result goes to a work field, from which the
 // scalar filter or, without it, a copy takes it to c (FP32 384x144x96: scalar
-// step 126 us with single stages, 118 with pairs and the copy).
+// step 126 us with single stages, 118 with pairs and the copy).  The copy is not
+// recorded: a recording without the filter keeps single stages, which nothing
+// replays on grids large enough for pairs.
 bool sca_pairs(const dnslab_ctx* x) { return (x->P.filter != 0 || !x->rec) && stage_pairs(x); }
 // Partial-sum slots the scalar stages fill (divergence and, without the filter, CO2).
 int sca_nblocks(const dnslab_ctx* x) { return sca_pairs(x) ? x->Lo.LP.nblocks : x->Lo.L.nblocks; }
@@ -2038,6 +2040,10 @@ struct BatchGroup {
     bool direct = false;
 };
 constexpr long long POOL_DIRECT_CELLS = 1LL << 20;
+// The kernels that begin at some grid size have no batched instances.
+static_assert(DNSLAB_PAIR_MIN_CELLS64 >= POOL_DIRECT_CELLS && DNSLAB_PAIR_MIN_CELLS32 >= POOL_DIRECT_CELLS &&
+                  DNSLAB_RING_MIN_CELLS >= POOL_DIRECT_CELLS && DNSLAB_CORR_RING_CELLS >= POOL_DIRECT_CELLS,
+              "scenarios with stage pairs or ring kernels are issued on their own");
 // Budget reserved per scenario for its share of the batched launch tables
 // (about 70 launch records of at most ~0.5 KB per step sequence).
 constexpr size_t POOL_TABLE_RESERVE = 64 * 1024;

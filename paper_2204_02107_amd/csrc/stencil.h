@@ -241,7 +241,9 @@ struct DiagArgs {
 hipError_t launch_diag(const DiagArgs& a, hipStream_t s, Recorder* rec = nullptr);
 
 // Batched replay of one recorded position over ns scenarios: tab holds ns
-// BRec<Args> entries (device), starts the ns+1 block offsets (device).
+// BRec<Args> entries (device), starts the ns+1 block offsets (device).  The
+// stage pairs and the ring forms have no batched instance (hipErrorInvalidValue):
+// scenarios large enough for them are issued on their own.
 hipError_t launch_batched_stencil(int kind, const void* tab, const unsigned* starts, int ns, unsigned total_blocks,
                                   dim3 block, size_t lds, hipStream_t s);
 // Reduce Courant partials only: sets sc->rate and the next dt.

@@ -46,8 +46,6 @@ namespace {
 #endif
 constexpr int FILT_LDS = 16;   // filter kind mode bit: LDS-tiled variant
 constexpr int FILT_RING = 32;  // filter kind mode bit: LDS-tiled variant with register rings
-constexpr int FILT_PART = 64;  // filter kind mode bit: its form for grids that the tile does not divide
-constexpr int PAIR_PART = 2;   // stage pair kind mode bit: the same
 constexpr int STAGE_LDS = 8;   // RK4 stage kind mode bit: LDS-tiled variant
 
 constexpr double INV_PI6 = 1.0 / (3.14159265358979323846 * 3.14159265358979323846 *
@@ -1944,24 +1942,10 @@ __device__ __forceinline__ MomArgs<T> from_table(const MomArgs<T>& t) {
     return a;
 }
 template <typename T>
-__device__ __forceinline__ MomPairArgs<T> from_table(const MomPairArgs<T>& t) {
-    MomPairArgs<T> a = t;
-    DNSLAB_G3(vin), DNSLAB_G3(un), DNSLAB_G3(accin), DNSLAB_G3(acc), DNSLAB_G3(out), DNSLAB_G(flags), DNSLAB_G(dtp),
-        DNSLAB_GFORCE;
-    return a;
-}
-template <typename T>
 __device__ __forceinline__ ScaArgs<T> from_table(const ScaArgs<T>& t) {
     ScaArgs<T> a = t;
     DNSLAB_G3(u), DNSLAB_G(cs), DNSLAB_G(cn), DNSLAB_G(acc), DNSLAB_G(out), DNSLAB_G(flags), DNSLAB_G(dtp),
         DNSLAB_G(part.p), DNSLAB_GFORCE;
-    return a;
-}
-template <typename T>
-__device__ __forceinline__ ScaPairArgs<T> from_table(const ScaPairArgs<T>& t) {
-    ScaPairArgs<T> a = t;
-    DNSLAB_G3(u), DNSLAB_G(cin), DNSLAB_G(cn), DNSLAB_G(accin), DNSLAB_G(acc), DNSLAB_G(out), DNSLAB_G(flags),
-        DNSLAB_G(dtp), DNSLAB_G(part.p), DNSLAB_GFORCE;
     return a;
 }
 template <typename T>
@@ -2041,22 +2025,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<
     mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS, PART>(a, hw_block());
 }
 template <typename T, int PAIR, bool PART>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, true, PAIR>()))) void k_mom_pair_b(const BRec<MomPairArgs<T>>* __restrict__ tab,
-                                                    const unsigned* __restrict__ st, int ns) {
-    DNSLAB_BATCH_COORD(tab, st, ns)
-    const MomPairArgs<T> a = from_table(tab[s_].a);
-    mom_pair_body<T, PAIR, pair_dist<T, true, PAIR>(), DNSLAB_PROWS, PART>(a, bi_);
-}
-template <typename T, int PAIR, bool PART>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, false, PAIR>()))) void k_sca_pair(const ScaPairArgs<T> a) {
     sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS, PART>(a, hw_block());
-}
-template <typename T, int PAIR, bool PART>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(pair_waves<T, false, PAIR>()))) void k_sca_pair_b(const BRec<ScaPairArgs<T>>* __restrict__ tab,
-                                                    const unsigned* __restrict__ st, int ns) {
-    DNSLAB_BATCH_COORD(tab, st, ns)
-    const ScaPairArgs<T> a = from_table(tab[s_].a);
-    sca_pair_body<T, PAIR, pair_dist<T, false, PAIR>(), DNSLAB_PROWS, PART>(a, bi_);
 }
 template <typename T, int MODE>
 __global__ __launch_bounds__(1024) void k_sca_stage(const ScaArgs<T> a) { sca_stage_body<T, MODE>(a, hw_block()); }
@@ -2088,13 +2058,6 @@ __global__ __launch_bounds__(1024) void k_filter_lds_b(const BRec<FiltArgs<T>>* 
 template <typename T, int NF, bool PART>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_filter_ring(const FiltArgs<T> a) {
     filter_ring_body<T, NF, DNSLAB_FROWS, PART>(a, hw_block());
-}
-template <typename T, int NF, bool PART>
-__global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_filter_ring_b(const BRec<FiltArgs<T>>* __restrict__ tab,
-                                                       const unsigned* __restrict__ st, int ns) {
-    DNSLAB_BATCH_COORD(tab, st, ns)
-    const FiltArgs<T> a = from_table(tab[s_].a);
-    filter_ring_body<T, NF, DNSLAB_FROWS, PART>(a, bi_);
 }
 template <typename T>
 __global__ __launch_bounds__(1024) void k_correct(const CorrArgs<T> a) { correct_body<T>(a, hw_block()); }
@@ -2142,21 +2105,8 @@ __device__ __forceinline__ void refine_correct_ring(const RefineCorrArgs& a, con
 }
 template <typename T>
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_correct_ring(const CorrArgs<T> a) { correct_ring<T>(a, hw_block()); }
-template <typename T>
-__global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_correct_ring_b(const BRec<CorrArgs<T>>* __restrict__ tab,
-                                                        const unsigned* __restrict__ st, int ns) {
-    DNSLAB_BATCH_COORD(tab, st, ns)
-    const CorrArgs<T> a = from_table(tab[s_].a);
-    correct_ring<T>(a, bi_);
-}
 __global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_refine_correct_ring(const RefineCorrArgs a) {
     refine_correct_ring(a, hw_block());
-}
-__global__ __launch_bounds__(64 * DNSLAB_FROWS) void k_refine_correct_ring_b(const BRec<RefineCorrArgs>* __restrict__ tab,
-                                                               const unsigned* __restrict__ st, int ns) {
-    DNSLAB_BATCH_COORD(tab, st, ns)
-    const RefineCorrArgs a = from_table(tab[s_].a);
-    refine_correct_ring(a, bi_);
 }
 __global__ __launch_bounds__(1024) void k_refine_correct(const RefineCorrArgs a) {
     refine_correct_body(a, hw_block());
@@ -2263,7 +2213,7 @@ hipError_t launch_mom_pair(int pair, const MomPairArgs<T>& a, const StencilLaunc
     b.kc = L.kc;
     const size_t lds = (size_t)6 * ((L.block.x + 4) * (L.block.y + 4) + (L.block.x + 2) * (L.block.y + 2)) * sizeof(T);
     if (rec) {
-        record_launch(rec, kind_code(KK_MOMPAIR, pair | (tile_divides(a.g, L) ? 0 : PAIR_PART), sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_MOMPAIR, pair, sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
     const bool part = !tile_divides(a.g, L);
@@ -2282,7 +2232,7 @@ hipError_t launch_sca_pair(int pair, const ScaPairArgs<T>& a, const StencilLaunc
     const size_t tv = (size_t)(L.block.x + 4) * (L.block.y + 4), tw = (size_t)(L.block.x + 2) * (L.block.y + 2);
     const size_t lds = (6 * tv + 2 * tw) * sizeof(T) + 2 * tv;
     if (rec) {
-        record_launch(rec, kind_code(KK_SCAPAIR, pair | (tile_divides(a.g, L) ? 0 : PAIR_PART), sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_SCAPAIR, pair, sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
     const bool part = !tile_divides(a.g, L);
@@ -2320,14 +2270,14 @@ hipError_t launch_filter(const FiltArgs<T>& a, const StencilLaunch& L, hipStream
     const bool use_lds = DNSLAB_FILTER_LDS && tile_fits(a.g, L, 3);
     const bool use_ring = filter_ring_supported(a.g, L, sizeof(T));
     const int nf = a.nf == 3 ? 3 : 1;
-    const bool part = use_ring && !tile_divides(a.g, L);
     const size_t lds = use_lds ? (size_t)2 * nf * (L.block.x + 6) * (L.block.y + 6) * sizeof(T) : 0;
     if (rec) {
-        record_launch(rec, kind_code(KK_FILT, nf | (use_lds ? FILT_LDS : 0) | (use_ring ? FILT_RING : 0) |
-                                     (part ? FILT_PART : 0), sizeof(T) == 4), L.grid, L.block, lds, b);
+        record_launch(rec, kind_code(KK_FILT, nf | (use_lds ? FILT_LDS : 0) | (use_ring ? FILT_RING : 0),
+                                     sizeof(T) == 4), L.grid, L.block, lds, b);
         return hipSuccess;
     }
     if (use_ring) {
+        const bool part = !tile_divides(a.g, L);
         if (nf == 3 && !part) hipLaunchKernelGGL((k_filter_ring<T, 3, false>), L.grid, L.block, lds, s, b);
         else if (!part) hipLaunchKernelGGL((k_filter_ring<T, 1, false>), L.grid, L.block, lds, s, b);
         else if (nf == 3) hipLaunchKernelGGL((k_filter_ring<T, 3, true>), L.grid, L.block, lds, s, b);
@@ -2449,22 +2399,6 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
             }
             break;
         }
-        case KK_MOMPAIR: {
-            auto t = (const BRec<MomPairArgs<T>>*)tab;
-            if (mode == 0) hipLaunchKernelGGL((k_mom_pair_b<T, 0, false>), grid, blk, lds, s, t, st, ns);
-            else if (mode == 1) hipLaunchKernelGGL((k_mom_pair_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
-            else if (mode == PAIR_PART) hipLaunchKernelGGL((k_mom_pair_b<T, 0, true>), grid, blk, lds, s, t, st, ns);
-            else hipLaunchKernelGGL((k_mom_pair_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
-            break;
-        }
-        case KK_SCAPAIR: {
-            auto t = (const BRec<ScaPairArgs<T>>*)tab;
-            if (mode == 0) hipLaunchKernelGGL((k_sca_pair_b<T, 0, false>), grid, blk, lds, s, t, st, ns);
-            else if (mode == 1) hipLaunchKernelGGL((k_sca_pair_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
-            else if (mode == PAIR_PART) hipLaunchKernelGGL((k_sca_pair_b<T, 0, true>), grid, blk, lds, s, t, st, ns);
-            else hipLaunchKernelGGL((k_sca_pair_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
-            break;
-        }
         case KK_SCA: {
             auto t = (const BRec<ScaArgs<T>>*)tab;
             switch (mode) {
@@ -2480,11 +2414,7 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
             auto t = (const BRec<FiltArgs<T>>*)tab;
             const bool three = (mode & 7) == 3;
             if (mode & FILT_RING) {
-                const bool part = mode & FILT_PART;
-                if (three && !part) hipLaunchKernelGGL((k_filter_ring_b<T, 3, false>), grid, blk, lds, s, t, st, ns);
-                else if (!part) hipLaunchKernelGGL((k_filter_ring_b<T, 1, false>), grid, blk, lds, s, t, st, ns);
-                else if (three) hipLaunchKernelGGL((k_filter_ring_b<T, 3, true>), grid, blk, lds, s, t, st, ns);
-                else hipLaunchKernelGGL((k_filter_ring_b<T, 1, true>), grid, blk, lds, s, t, st, ns);
+                return hipErrorInvalidValue;
             } else if (mode & FILT_LDS) {
                 if (three) hipLaunchKernelGGL((k_filter_lds_b<T, 3>), grid, blk, lds, s, t, st, ns);
                 else hipLaunchKernelGGL((k_filter_lds_b<T, 1>), grid, blk, lds, s, t, st, ns);
@@ -2495,10 +2425,8 @@ hipError_t batched_typed(int base, int mode, const void* tab, const unsigned* st
             break;
         }
         case KK_CORR:
-            if (mode == 1)
-                hipLaunchKernelGGL((k_correct_ring_b<T>), grid, blk, lds, s, (const BRec<CorrArgs<T>>*)tab, st, ns);
-            else
-                hipLaunchKernelGGL((k_correct_b<T>), grid, blk, 0, s, (const BRec<CorrArgs<T>>*)tab, st, ns);
+            if (mode == 1) return hipErrorInvalidValue;
+            hipLaunchKernelGGL((k_correct_b<T>), grid, blk, 0, s, (const BRec<CorrArgs<T>>*)tab, st, ns);
             break;
         case KK_DIV:
             hipLaunchKernelGGL((k_div_b<T>), grid, blk, 0, s, (const BRec<DivArgs<T>>*)tab, st, ns);
@@ -2519,10 +2447,8 @@ hipError_t launch_batched_stencil(int kind, const void* tab, const unsigned* st,
         return hipGetLastError();
     }
     if (base == KK_REFCORR) {
-        if (mode == 1)
-            hipLaunchKernelGGL(k_refine_correct_ring_b, dim3(nb), blk, lds, s, (const BRec<RefineCorrArgs>*)tab, st, ns);
-        else
-            hipLaunchKernelGGL(k_refine_correct_b, dim3(nb), blk, 0, s, (const BRec<RefineCorrArgs>*)tab, st, ns);
+        if (mode == 1) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_refine_correct_b, dim3(nb), blk, 0, s, (const BRec<RefineCorrArgs>*)tab, st, ns);
         return hipGetLastError();
     }
     if (base == KK_ADVANCE) {
