@@ -474,19 +474,15 @@ __device__ __forceinline__ void ring_cell(int r, int BX, int BY, int& lx, int& l
 // Waves per SIMD the FP32 pair kernels are compiled for (0: the compiler's
 // choice).  Four keep them within 128 registers, two 512-thread blocks per
 // CU (measured on 1024x512x256: momentum pairs 1747 -> 1621 us, scalar
-// pairs 1318 -> 1243 us, against one block per CU at 133-151 registers).
+// pairs 1318 -> 1243 us, against one block per CU at 133-151 registers).  The
+// scalar pair 1 takes 128 registers by itself, the momentum pair 1 spills 16
+// to 20 bytes per lane (unconstrained, at 133 registers, it made the step on
+// that grid slower: 8.60 -> 8.35 Gcell-steps/s on two streams).
 #ifndef DNSLAB_PAIR_WAVES32
 #define DNSLAB_PAIR_WAVES32 4
 #endif
 #ifndef DNSLAB_PAIR_WAVES32_MOM1
 #define DNSLAB_PAIR_WAVES32_MOM1 DNSLAB_PAIR_WAVES32
-#endif
-// The FP32 scalar pair 1 needs 138 registers: held to 128 it spilled 19 per
-// lane.  Unconstrained (one block per CU) it is 3% slower alone, but the
-// FP32 step on 1024x512x256, where it runs beside the momentum pair 1 on the
-// second stream, went from 8.10 to 8.24 Gcell-steps/s.
-#ifndef DNSLAB_PAIR_WAVES32_SCA1
-#define DNSLAB_PAIR_WAVES32_SCA1 0
 #endif
 #ifndef DNSLAB_PAIR_DIST_SCA32
 #define DNSLAB_PAIR_DIST_SCA32 DNSLAB_PAIR_DIST_OTHER
@@ -499,7 +495,7 @@ constexpr int pair_dist() {
 template <typename T, bool MOM, int PAIR>
 constexpr int pair_waves() {
     constexpr int w = sizeof(T) != 4 ? 0
-                      : (PAIR == 1 ? (MOM ? DNSLAB_PAIR_WAVES32_MOM1 : DNSLAB_PAIR_WAVES32_SCA1) : DNSLAB_PAIR_WAVES32);
+                      : (MOM && PAIR == 1 ? DNSLAB_PAIR_WAVES32_MOM1 : DNSLAB_PAIR_WAVES32);
     return w > 0 ? w : 1;
 }
 
