@@ -539,9 +539,9 @@ def main():
                     help="run every launch of a step in order on one stream (for kernel traces whose durations "
                          "are those of each kernel alone)")
     ap.add_argument("--stage-pairs", type=int, default=-1, choices=[-1, 0, 1],
-                    help="RK4 stages two per pass: -1 by grid size (default), 0 never, 1 wherever the tile divides the grid")
+                    help="RK4 stages two per pass: -1 by grid size (default), 0 never, 1 wherever a 64 x 8 tile fits the grid")
     ap.add_argument("--fft-pipeline", type=int, default=-1, choices=[-1, 0, 1],
-                    help="pipelined FFT column passes: -1 by tile count (default), 0 never, 1 wherever they apply")
+                    help="pipelined FFT column passes: -1 the library's choice (default), 0 never, 1 wherever they apply")
     ap.add_argument("--serving", default="config4", choices=["none", "short", "config4", "config4-all"],
                     help="serving stream: config4 = 64 requests x 2000 steps, pool FP32 form vs FIFO FP64; "
                          "config4-all adds the pool in FP64; short = 16 x 300")

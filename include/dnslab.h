@@ -238,7 +238,8 @@ int dnslab_particles_step(dnslab_ctx* ctx, int64_t n, double* pos, double* vel, 
  * order is free; sorted particles gather their fluid velocities from
  * neighbouring cells, which the step kernel turns into coalesced reads.  On
  * the context's stream; allocates device scratch on first use and when n
- * grows (then synchronises the stream first).  The sort is a stable radix
+ * grows (then synchronises the stream first): about 73 bytes per particle up
+ * to 2^22 particles if that can be had, else about 24.  The sort is a stable radix
  * sort on the bits the cell count needs (8 per pass).  0 <= n <= 2^28, else
  * DNSLAB_EINVAL. */
 int dnslab_particles_sort(dnslab_ctx* ctx, int64_t n, double* pos, double* vel, double* diam);
@@ -277,6 +278,8 @@ int dnslab_body_force(dnslab_ctx* ctx, const int32_t box[6], double* out_dev);
  * "fft_x_inv", "filter", "filter_c", "correct", "div", "ib_rhs", "advance",
  * "diag", "refine_res", "particles") is bracketed by HIP events on the stream it is
  * launched on, and the total and count accumulate (kernel_name NULL: off).
+ * A solve in three passes reports its middle one as "fft_yz" and has no
+ * "fft_y" or "fft_z".
  * Steps are issued launch by launch while a kernel is profiled.  Read
  * synchronises. */
 int dnslab_profile_enable(dnslab_ctx* ctx, const char* kernel_name);
@@ -295,8 +298,8 @@ int dnslab_set_graph_steps(dnslab_ctx* ctx, int32_t k);
 /* enable = 1 (the default): the scalar half of a step (scalar RK4, its filter
  * and the diagnostics record) runs on a second stream of the context beside
  * the next step's velocity work, as the data dependences allow, except for
- * FP64 grids of 2^26 cells or more, whose steps stay on one stream (there
- * that is faster).  0: every launch of a step runs in order on the context's
+ * grids of 2^26 cells or more, whose steps stay on one stream (there that is
+ * faster).  0: every launch of a step runs in order on the context's
  * stream (for timing kernels alone).  Results are bitwise the same either
  * way.  Enqueues any deferred scalar work first.  DNSLAB_EINVAL unless enable
  * is 0 or 1. */
@@ -307,9 +310,9 @@ int dnslab_set_overlap(dnslab_ctx* ctx, int32_t enable);
  * ring and the second on the tile, reading and writing the fields once per
  * pair).  mode -1 (the default): by grid size (from 2^20 cells in FP64 and
  * 2^21 in the FP32 form, nz >= 4); 0: never (one kernel
- * per stage); 1: wherever a 64 x 8 tile fits the grid (nx >= 64,
- * ny >= 8).  Without the filter the pool keeps
- * the scalar's single stages.  Results agree
+ * per stage); 1: wherever a 64 x 8 tile fits the grid (nx >= 64, ny >= 8).
+ * Fields of 4 GiB or more (2^29 cells in FP64, 2^30 in the FP32 form) take one
+ * kernel per stage in every mode.  Results agree
  * to rounding (every value is computed with the same expressions).  Enqueues
  * any deferred scalar work first.  DNSLAB_EINVAL unless mode is -1, 0 or 1. */
 int dnslab_set_stage_pairs(dnslab_ctx* ctx, int32_t mode);
@@ -319,8 +322,9 @@ int dnslab_set_stage_pairs(dnslab_ctx* ctx, int32_t mode);
  * tiles, moving them into LDS with asynchronous loads).  mode -1 (the
  * default): the library's choice (currently never: one tile per block
  * measured faster on the grids tried); 0: never; 1: wherever the pass
- * applies (row-major spectrum, plain launches, transform lengths 64 to 1024
- * of the form 2^a 3^b with a compiled chain).  Same arithmetic either way:
+ * applies (grids whose lengths have no solve on register tiles, row-major
+ * spectrum, plain launches, transform lengths 64 to 1024 of the form 2^a 3^b
+ * with a compiled chain).  Same arithmetic either way:
  * results are bitwise the same.
  * Enqueues any deferred scalar work first.  DNSLAB_EINVAL unless mode is -1,
  * 0 or 1. */

@@ -182,19 +182,17 @@ Grid make_grid(const dnslab_params* P) {
 #ifndef DNSLAB_XLS_MOD
 #define DNSLAB_XLS_MOD 2       // x-pass LDS line stride modulo 16 (make_layout)
 #endif
-// Least z cells per thread of the filter (and of the velocity correction,
-// which shares its launch): the radius-3 filter
-// re-reads 6 halo planes per chunk.  24 in both forms since the filter runs
-// as a register-ring march (512x256x192: filter 345 -> 305 us FP64,
-// 191 -> 172 us FP32; 1024x512x256 already has 32).
+// Least z cells per thread of the filter on large grids that its register-ring
+// form does not take (make_layout): the radius-3 filter reads 6 halo planes
+// per chunk.
 #ifndef DNSLAB_FKC_MIN
 #define DNSLAB_FKC_MIN 24
 #endif
 #ifndef DNSLAB_FKC_MIN32
 #define DNSLAB_FKC_MIN32 24
 #endif
-// below this many blocks of 64 x DNSLAB_FROWS tiles, the filter and the
-// correction take 64 x 8 tiles with the shorter chunks below
+// below this many blocks of 64 x DNSLAB_FROWS tiles it takes 64 x 8 tiles there,
+// with the shorter chunks below
 #ifndef DNSLAB_RING_MIN_BLOCKS
 #define DNSLAB_RING_MIN_BLOCKS 1024
 #endif
@@ -429,7 +427,9 @@ Layout make_layout(const dnslab_params* P, int n_forced) {
     // 384x144x96 73 in 24 and 96; 192x96x64 32 and 33.  128x64x64 gets 64 blocks
     // and is faster in small tiles (FP64 29 and 27).  The correction, with less
     // to read, gains from 2^21 cells on (384x144x96 FP64 66 -> 60 us; 256x128x64
-    // 25 -> 27).
+    // 25 -> 27).  Flat grids too, though each of their blocks reads 6 planes for
+    // one to three of its own: one field, FP64, 1296x1152x1 17 us against 21 in
+    // the plain kernel, 1296x972x3 23 and 41, 2048x1024x1 22 either way.
     const bool ring_geometry = P->nx >= 64 && P->ny >= DNSLAB_FROWS && g.n >= DNSLAB_RING_MIN_CELLS &&
                                ring_offsets_fit(g, Lo.esz);
     if (ring_geometry) {

@@ -36,9 +36,9 @@
 //
 // Measured (one solve, against the five passes; 64^3, 192x96x64 and the FP32
 // 256x128x96 against the fused y/z plane pass they took before):
-//   FP64: 64^3 29 -> 17 us, 216x108x72 104 -> 36, 256x128x96 67 -> 46,
+//   FP64: 64^3 29 -> 17 us, 216x108x72 104 -> 33, 256x128x96 67 -> 46,
 //         512x256x192 402 -> 297;  FP32: 512x256x192 245 -> 170.
-// On 512x256x192 FP64 the x passes move 4.8 to 4.9 TB/s, the z pass 3.3: its
+// On 512x256x192 FP64 the x passes move 4.8 to 4.9 TB/s, the z pass 3.5: its
 // blocks of 1024 threads and 104 KB run one to a CU, so that its exchanges
 // (about 40 us of it) are not hidden behind its loads and stores.  The same
 // pass with rows of 32 bytes (52 KB tiles) took 160 us instead of 121: short
